@@ -37,85 +37,25 @@
 #include <atomic>
 #include <type_traits>
 
+#include "mx_gemm.h"
+#include "mx_gemm_ksplit.h"
+#include "mx_gemm_ring.h"
 #include "mxnorm.h"
 #include "status.h"
 
 namespace mxg {
 
-typedef int v8i __attribute__((ext_vector_type(8)));
-typedef float v4f __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-#define LDS_AS __attribute__((address_space(3)))
-
 constexpr int BM = 256;    // tile rows of A (M)
 constexpr int BN = 256;    // tile rows of B (N)
-constexpr int KB = 128;    // bytes of each row per K step
 constexpr int NT = 512;    // threads: 8 waves, two per SIMD
 constexpr int WTM = 128;   // wave tile along M
 constexpr int WTN = 64;    // wave tile along N
 constexpr int FM = WTM / 16, FN = WTN / 16;
-constexpr int GROUP_M = 4; // tile rows per group in the visiting order
-constexpr int NXCD = 8;
 
-// scale bytes per row and K step: 4 blocks of 32 (E4M3), 8 blocks (E2M1)
 template <int ELEM> struct Op {
-    static constexpr int SB = ELEM == MX_ELEM_E2M1 ? 8 : 4;
+    static constexpr int SB = kSB<ELEM>;
     static constexpr int STAGE = (BM + BN) * KB + (BM + BN) * SB;
 };
-
-struct Args {
-    const uint8_t *a, *as, *b, *bs;
-    const uint16_t *bgain; // bf16 [N] or NULL
-    void *out;
-    int64_t M, N;
-    int64_t rb;   // code bytes per row
-    int64_t rs;   // scale bytes per row
-    int steps;    // K steps of KB bytes
-    int tiles_m, tiles_n;
-    int xcd_ranges; // 1: each XCD runs a contiguous range of tiles; 0: round robin
-    int grid_max;   // workgroups resident at once: one per compute unit
-};
-
-// Global -> LDS DMA loads: lane i of the wave reads gbase + off_i (gbase
-// wave-uniform, in SGPRs; off_i a 32-bit lane offset) and writes the bytes at
-// LDS address lds_base + bytes * i (lds_base wave-uniform, passed in M0).
-// Written as inline asm rather than with the compiler builtin: for the builtin
-// the compiler cannot tell that the LDS reads of one stage do not alias the
-// DMA into the other, and would wait for the prefetch before every read.  The
-// waits are explicit (wait_vmcnt) instead.  An LDS DMA needs one wait state
-// after the scalar write of M0 that the compiler places just before the asm:
-// hence the s_nop.
-__device__ __forceinline__ void lds_load16(const void *gbase, uint32_t off, uint32_t lds_base)
-{
-    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(gbase),
-                 "{m0}"(lds_base)
-                 : "memory");
-}
-
-__device__ __forceinline__ void lds_load4(const void *gbase, uint32_t off, uint32_t lds_base)
-{
-    asm volatile("s_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(off), "s"(gbase),
-                 "{m0}"(lds_base)
-                 : "memory");
-}
-
-// Wait until at most N_ of this wave's vector memory operations (loads and
-// stores, which complete in issue order) are outstanding.
-template <int N_> __device__ __forceinline__ void wait_vmcnt()
-{
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N_) : "memory");
-}
-
-// Workgroup barrier without the memory fence of __syncthreads(): the fence
-// would wait for every outstanding load, including the DMA of the next step.
-// LDS written by the DMA is covered by the vmcnt wait each wave makes before
-// arriving; the lgkmcnt(0) completes this wave's own LDS reads, so that a
-// stage read before the barrier can be refilled after it.  The "memory"
-// clobber keeps the compiler from moving LDS accesses across it.
-__device__ __forceinline__ void barrier()
-{
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
 
 // Per-lane part of the DMA addresses, fixed for the whole K loop: byte
 // offsets, relative to the tile's first row, of the rows this lane moves.
@@ -177,66 +117,6 @@ __device__ __forceinline__ void issue_step(const uint8_t *ta, const uint8_t *tb,
 #pragma unroll
     for (int u = 0; u < DW; ++u)
         lds_load4(ts, R.s[u] + ks, xs + u * (64 / DW) * SB);
-}
-
-__device__ __forceinline__ v8i join(u32x4 lo, u32x4 hi)
-{
-    return __builtin_bit_cast(v8i, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-}
-
-// two floats to bf16 (round to nearest even, on gfx950's conversion unit),
-// the first in the low half
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b)
-{
-    const __bf16 x = (__bf16)a, y = (__bf16)b;
-    return (uint32_t)__builtin_bit_cast(uint16_t, x) |
-           ((uint32_t)__builtin_bit_cast(uint16_t, y) << 16);
-}
-
-// One operand fragment for a 16-row group and one K step: lane (g, q) holds
-// the 16-byte chunks g and 4+g of row r (E4M3: k = 16g..16g+15 and
-// 64+16g..64+16g+15 of the step, the matrix core's own k order for this
-// operand size; E2M1: chunk g is the 32-element block g of the first
-// instruction, chunk 4+g block g of the second) and the E8M0 scale bytes of
-// the blocks it supplies (E4M3: block g; E2M1: blocks g and 4+g).
-struct Frag {
-    v8i v;
-    int s0, s1;
-};
-
-// Lane-relative LDS offsets of one operand's fragments within a stage: the
-// lane reads row r0 + qd (+16 j for fragment j) at chunks g and 4 + g,
-// swizzled by (r0 + qd) & 7 = qd & 7 (r0 is a multiple of 16), and the
-// scale bytes g (and 4 + g) of that row.
-struct FragBase {
-    uint32_t lo, hi, sc;
-};
-
-template <int ELEM>
-__device__ __forceinline__ FragBase frag_base(uint32_t codes_off, uint32_t scales_off, int r0,
-                                              int qd, int g)
-{
-    constexpr int SB = Op<ELEM>::SB;
-    FragBase b;
-    b.lo = codes_off + (r0 + qd) * KB + 16 * (g ^ (qd & 7));
-    b.hi = codes_off + (r0 + qd) * KB + 16 * ((4 + g) ^ (qd & 7));
-    b.sc = scales_off + (r0 + qd) * SB + g;
-    return b;
-}
-
-// fragment J of an operand from the stage at st; the row offset J*16 rows is
-// a compile-time constant that the LDS reads take as their immediate offset
-template <int ELEM, int J>
-__device__ __forceinline__ Frag read_frag(const LDS_AS uint8_t *st, const FragBase &b)
-{
-    constexpr int SB = Op<ELEM>::SB;
-    Frag f;
-    const u32x4 lo = *reinterpret_cast<const LDS_AS u32x4 *>(st + b.lo + J * 16 * KB);
-    const u32x4 hi = *reinterpret_cast<const LDS_AS u32x4 *>(st + b.hi + J * 16 * KB);
-    f.v = join(lo, hi);
-    f.s0 = st[b.sc + J * 16 * SB];
-    f.s1 = ELEM == MX_ELEM_E2M1 ? (int)st[b.sc + J * 16 * SB + 4] : 0;
-    return f;
 }
 
 // acc += B-fragment x A-fragment over one E4M3 K step (B is the
@@ -349,95 +229,6 @@ __device__ __forceinline__ void step_products(v4f (&acc)[FN][FM], const LDS_AS u
     column(std::integral_constant<int, 7>{});
 }
 
-// Output stores bypass the caches' normal allocation (cache policy sc0 sc1
-// nt: system scope, non-temporal): H is written once and read by a later
-// kernel, and with the default policy the stores slow the operand stream
-// more (QKV shape, E4M3 -> bf16: 720 -> 673 us).
-constexpr int kStorePolicy = 0x13;
-
-// stores per wave and tile
-template <int OUT> constexpr int kTileStores = OUT == MX_OUT_F32 ? FM * FN : FM * FN / 2;
-
-// Store the workgroup's accumulators as H[m0 .., n0 ..] (f32 or bf16), times
-// the column gain if there is one.  Every lane runs the same stores (exactly
-// kTileStores of them when the tile lies inside H); lanes outside H are
-// masked.
-template <int OUT>
-__device__ __forceinline__ void store_tile(const Args &A, const v4f (&acc)[FN][FM], int64_t m0,
-                                           int64_t n0, int wm, int wn, int g, int qd)
-{
-    // lane (g, qd) of tile (i, j) holds H[m][n .. n+3] with
-    // m = m0 + wm + 16 j + qd and n = n0 + wn + 16 i + 4 g.  N is a multiple
-    // of 16, so a tile column base below N has its 16 columns inside H.
-    // The gains of the lane's columns are loaded before any store.
-    uint2 gw[FN];
-    if (A.bgain) {
-#pragma unroll
-        for (int i = 0; i < FN; ++i) {
-            const int64_t n = n0 + wn + 16 * i + 4 * g;
-            gw[i] = *reinterpret_cast<const uint2 *>(A.bgain + (n < A.N ? n : 0));
-        }
-    }
-    auto gained = [&](int i, int j) {
-        v4f v = acc[i][j];
-        if (A.bgain) {
-            v[0] = v[0] * __uint_as_float(gw[i].x << 16);
-            v[1] = v[1] * __uint_as_float(gw[i].x & 0xFFFF0000u);
-            v[2] = v[2] * __uint_as_float(gw[i].y << 16);
-            v[3] = v[3] * __uint_as_float(gw[i].y & 0xFFFF0000u);
-        }
-        return v;
-    };
-    constexpr int ES = OUT == MX_OUT_F32 ? 4 : 2; // bytes per element
-#pragma unroll
-    for (int j = 0; j < FM; ++j) {
-        // buffer over the 16 rows of tile row j (byte offsets below 2^31:
-        // the host limits N)
-        const int64_t mr = m0 + wm + 16 * j;
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-            static_cast<uint8_t *>(A.out) + mr * A.N * ES, 0, 0x7FFFFFFF, 0x00020000);
-        const int64_t m = mr + qd;
-        const uint32_t row = (uint32_t)(qd * A.N) * ES;
-        if constexpr (OUT == MX_OUT_F32) {
-#pragma unroll
-            for (int i = 0; i < FN; ++i) {
-                const int64_t n = n0 + wn + 16 * i + 4 * g;
-                const v4f v = gained(i, j);
-                if (m < A.M && n < A.N)
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rs,
-                                                           (int)(row + (uint32_t)n * 4), 0,
-                                                           kStorePolicy);
-            }
-        } else {
-            // bf16: tiles i and i+1 are stored together.  v_permlane16_swap
-            // trades the odd lane rows (g = 1, 3) of tile i's values with the
-            // even lane rows (g = 0, 2) of tile i+1's, after which lane row g
-            // holds 8 adjacent columns, 16 bytes, of tile i + (g & 1) from
-            // column 8 (g >> 1): one 16-byte store per lane and tile pair
-            // instead of two 8-byte stores.  The swap runs on every lane; only
-            // the stores are masked.
-            static_assert(FN % 2 == 0, "tiles are stored in pairs");
-#pragma unroll
-            for (int i = 0; i < FN; i += 2) {
-                uint32_t lo[2], hi[2];
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const v4f v = gained(i + h, j);
-                    lo[h] = pack_bf16(v[0], v[1]);
-                    hi[h] = pack_bf16(v[2], v[3]);
-                }
-                const auto sl = __builtin_amdgcn_permlane16_swap(lo[0], lo[1], false, false);
-                const auto sh = __builtin_amdgcn_permlane16_swap(hi[0], hi[1], false, false);
-                const int64_t n = n0 + wn + 16 * (i + (g & 1)) + 8 * (g >> 1);
-                if (m < A.M && n < A.N)
-                    __builtin_amdgcn_raw_buffer_store_b128(u32x4{sl[0], sh[0], sl[1], sh[1]}, rs,
-                                                           (int)(row + (uint32_t)n * 2), 0,
-                                                           kStorePolicy);
-            }
-        }
-    }
-}
-
 template <int ELEM, int OUT>
 __global__ void __launch_bounds__(NT) mx_gemm_kernel(Args A)
 {
@@ -445,26 +236,9 @@ __global__ void __launch_bounds__(NT) mx_gemm_kernel(Args A)
     constexpr int STAGE = Op<ELEM>::STAGE;
     __shared__ __attribute__((aligned(16))) uint8_t lds[2 * STAGE];
 
-    // Tiles.  The grid is at most one workgroup per compute unit, and
-    // workgroup b takes tiles v = b, b + grid, b + 2 grid, ...  Dispatch is
-    // round robin over the XCDs (each with its own L2).  With xcd_ranges, v
-    // is renumbered so that each XCD runs a contiguous range of tiles; either
-    // way the tiles are visited in groups of GROUP_M tile rows that share
-    // operand blocks.
-    const int G = A.tiles_m * A.tiles_n;
-    auto tile_of = [&](int v, int64_t &m0, int64_t &n0) {
-        int pid = v;
-        if (A.xcd_ranges) {
-            const int xcd = v % NXCD, loc = v / NXCD;
-            const int q = G / NXCD, rem = G % NXCD;
-            pid = xcd < rem ? xcd * (q + 1) + loc : rem * (q + 1) + (xcd - rem) * q + loc;
-        }
-        const int in_group = GROUP_M * A.tiles_n;
-        const int first_m = (pid / in_group) * GROUP_M;
-        const int gsz = min(A.tiles_m - first_m, GROUP_M);
-        m0 = (int64_t)(first_m + (pid % in_group) % gsz) * BM;
-        n0 = (int64_t)((pid % in_group) / gsz) * BN;
-    };
+    // The grid is at most one workgroup per compute unit, and workgroup b
+    // takes tiles v = b, b + grid, b + 2 grid, ...
+    const int G = A.cells;
 
     const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6); // wave-uniform
@@ -479,7 +253,7 @@ __global__ void __launch_bounds__(NT) mx_gemm_kernel(Args A)
 
     int v = blockIdx.x;
     int64_t m0, n0;
-    tile_of(v, m0, n0);
+    tile_of(A, BM, BN, v, m0, n0);
     Rows<ELEM> R = lane_rows<ELEM>(A, m0, n0, w, l);
 
     // Pipeline, one barrier per K step.  At the top of a step every wave has
@@ -507,7 +281,7 @@ __global__ void __launch_bounds__(NT) mx_gemm_kernel(Args A)
             // completed: operations complete in order, so at most that many
             // may remain (a partial tile ran fewer stores: wait for all).
             if (s == 0 && prev_full)
-                wait_vmcnt<kTileStores<OUT>>();
+                wait_vmcnt<kTileStores<OUT, FM, FN>>();
             else
                 wait_vmcnt<0>();
             barrier();
@@ -516,14 +290,14 @@ __global__ void __launch_bounds__(NT) mx_gemm_kernel(Args A)
                 issue_step<ELEM>(A.a + m0 * A.rb, A.b + n0 * A.rb, A.as + m0 * A.rs,
                                  A.bs + n0 * A.rs, R, s + 1, nxt, w);
             } else if (nv < G) {
-                tile_of(nv, m1, n1);
+                tile_of(A, BM, BN, nv, m1, n1);
                 R = lane_rows<ELEM>(A, m1, n1, w, l);
                 issue_step<ELEM>(A.a + m1 * A.rb, A.b + n1 * A.rb, A.as + m1 * A.rs,
                                  A.bs + n1 * A.rs, R, 0, nxt, w);
             }
             step_products<ELEM>(acc, st0 + cur * STAGE, ba, bb);
         }
-        store_tile<OUT>(A, acc, m0, n0, wm, wn, g, qd);
+        store_tile<OUT, FM, FN>(A, acc, m0, n0, wm, wn, g, qd);
         prev_full = m0 + BM <= A.M && n0 + BN <= A.N;
         if (nv >= G)
             break;
@@ -536,10 +310,107 @@ __global__ void __launch_bounds__(NT) mx_gemm_kernel(Args A)
 template <int ELEM, int OUT>
 hipError_t launch(const Args &A, hipStream_t stream)
 {
-    const int G = A.tiles_m * A.tiles_n;
+    const int G = A.cells;
     const int grid = G < A.grid_max ? G : A.grid_max;
     hipLaunchKernelGGL((mx_gemm_kernel<ELEM, OUT>), dim3((unsigned)grid), dim3(NT), 0, stream, A);
     return hipGetLastError();
+}
+
+// ------------------------------------------------------- choice of kernel --
+
+// Ring tiles: 4 waves, two workgroups per compute unit.
+using R64x128 = Ring<64, 128, 2, 2, 3>;
+using R128x128 = Ring<128, 128, 2, 2, 2>;
+// K-split tiles: 8 waves, one workgroup per compute unit.
+using K16x32 = KSplit<16, 32, 8, 3>;
+using K32x32 = KSplit<32, 32, 8, 2>;
+using K32x64 = KSplit<32, 64, 8, 1>;
+using K64x64 = KSplit<64, 64, 8, 1>;
+
+enum Shape { S_K16x32, S_K32x32, S_K32x64, S_K64x64, S_R64x128, S_R128x128, S_256x256, S_COUNT };
+
+// What a launch of each tile shape costs on MI355X, fitted to times at K =
+// 512 .. 8192 and 64 to 3400 tiles (E4M3; E2M1 moves the same bytes per step
+// and is within 15%): us once per launch, per round of tiles (their stores,
+// and for the K-split kernel the start of a tile's loads, which nothing
+// overlaps) and per K step of a round.  Below 256 x 256 the time per step is
+// the tile's operand bytes at about 55 GB/s per compute unit, so a larger
+// tile does more products per byte and a smaller one leaves fewer compute
+// units idle.
+struct Cost {
+    int bm, bn;
+    float once, round, step;
+};
+constexpr Cost kCost[S_COUNT] = {
+    {16, 32, 1.3f, 1.0f, 0.14f},  {32, 32, 1.4f, 1.1f, 0.14f},  {32, 64, 2.2f, 0.7f, 0.19f},
+    {64, 64, 0.4f, 2.6f, 0.275f}, {64, 128, 3.1f, 0.4f, 0.425f}, {128, 128, 4.1f, 0.8f, 0.59f},
+    {256, 256, 1.2f, 4.0f, 1.75f},
+};
+
+// us a launch over `cells` outputs of cm x cn takes on `cus` compute units
+inline double launch_cost(int shape, int64_t cells, int64_t cm, int64_t cn, int steps, int cus)
+{
+    const Cost &c = kCost[shape];
+    const int64_t tiles = cells * ((cm + c.bm - 1) / c.bm) * ((cn + c.bn - 1) / c.bn);
+    const int64_t rounds = (tiles + cus - 1) / cus;
+    return c.once + (double)rounds * (c.round + (double)steps * c.step);
+}
+
+template <int ELEM, int OUT> hipError_t launch_shape(int shape, const Args &A, hipStream_t stream)
+{
+    switch (shape) {
+    case S_K16x32: return launch_ksplit<ELEM, OUT, K16x32>(A, stream);
+    case S_K32x32: return launch_ksplit<ELEM, OUT, K32x32>(A, stream);
+    case S_K32x64: return launch_ksplit<ELEM, OUT, K32x64>(A, stream);
+    case S_K64x64: return launch_ksplit<ELEM, OUT, K64x64>(A, stream);
+    case S_R64x128: return launch_ring<ELEM, OUT, R64x128>(A, stream);
+    case S_R128x128: return launch_ring<ELEM, OUT, R128x128>(A, stream);
+    default: return launch<ELEM, OUT>(A, stream);
+    }
+}
+
+// One shape for the whole output, the cheapest; or whole rounds of 256 x 256
+// tiles and a second launch of the cheapest smaller shape over the tiles
+// left, where that is at least 5% cheaper.
+template <int ELEM, int OUT> hipError_t multiply(Args A, hipStream_t stream)
+{
+    const int cus = A.grid_max;
+    int best = S_256x256;
+    double cost = launch_cost(best, 1, A.M, A.N, A.steps, cus);
+    for (int s = 0; s < S_256x256; ++s) {
+        const double c = launch_cost(s, 1, A.M, A.N, A.steps, cus);
+        if (c < cost) {
+            cost = c;
+            best = s;
+        }
+    }
+    set_tiles(A, BM, BN, 1024);
+    const int whole = A.cells / cus * cus, left = A.cells - whole;
+    if (whole && left) {
+        int tail = 0;
+        double tcost = launch_cost(0, left, BM, BN, A.steps, cus);
+        for (int s = 1; s < S_256x256; ++s) {
+            const double c = launch_cost(s, left, BM, BN, A.steps, cus);
+            if (c < tcost) {
+                tcost = c;
+                tail = s;
+            }
+        }
+        if (launch_cost(S_256x256, whole, BM, BN, A.steps, cus) + tcost < 0.95 * cost) {
+            A.cells = whole;
+            const hipError_t e = launch<ELEM, OUT>(A, stream);
+            if (e != hipSuccess)
+                return e;
+            A.pid0 = whole;
+            A.cells = left;
+            A.sub_m = BM / kCost[tail].bm;
+            A.sub_n = BN / kCost[tail].bn;
+            return launch_shape<ELEM, OUT>(tail, A, stream);
+        }
+    }
+    if (best != S_256x256)
+        set_tiles(A, kCost[best].bm, kCost[best].bn, 1024);
+    return launch_shape<ELEM, OUT>(best, A, stream);
 }
 
 } // namespace mxg
@@ -624,27 +495,16 @@ mx_status mx_matmul_fwd(const uint8_t *a_codes, const uint8_t *a_scales, const u
     A.rb = elem == MX_ELEM_E2M1 ? K / 2 : K;
     A.rs = K / 32;
     A.steps = (int)(A.rb / mxg::KB);
-    A.tiles_m = (int)tm;
-    A.tiles_n = (int)tn;
-    // Tile order: each XCD runs a contiguous range of tiles.  Measured at
-    // d = 4096 on MI355X against plain round robin: the QKV shape 737 vs
-    // 801 us; the gate+up shape (N = 28672) 1583 vs 1715 us at M = 16384 and
-    // 3214 vs 3446 us at M = 32768 (E2M1: 958 vs 1019 us).  (Before the
-    // output stores took their non-temporal policy, round robin was the
-    // faster order from N = 16384 on.)
-    A.xcd_ranges = 1;
-    // one workgroup per compute unit (each holds 135-139 KB of LDS); with the
-    // count unknown, one workgroup per tile
     const int cus = compute_units(stream);
-    A.grid_max = cus > 0 ? cus : (int)(tm * tn);
+    A.grid_max = cus > 0 ? cus : 256;
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipError_t e;
     if (elem == MX_ELEM_E4M3)
-        e = out_dtype == MX_OUT_F32 ? mxg::launch<MX_ELEM_E4M3, MX_OUT_F32>(A, st)
-                                         : mxg::launch<MX_ELEM_E4M3, MX_OUT_BF16>(A, st);
+        e = out_dtype == MX_OUT_F32 ? mxg::multiply<MX_ELEM_E4M3, MX_OUT_F32>(A, st)
+                                         : mxg::multiply<MX_ELEM_E4M3, MX_OUT_BF16>(A, st);
     else
-        e = out_dtype == MX_OUT_F32 ? mxg::launch<MX_ELEM_E2M1, MX_OUT_F32>(A, st)
-                                         : mxg::launch<MX_ELEM_E2M1, MX_OUT_BF16>(A, st);
+        e = out_dtype == MX_OUT_F32 ? mxg::multiply<MX_ELEM_E2M1, MX_OUT_F32>(A, st)
+                                         : mxg::multiply<MX_ELEM_E2M1, MX_OUT_BF16>(A, st);
     if (e != hipSuccess)
         return mxk::fail(MX_EHIP, "kernel launch failed: %s", hipGetErrorString(e));
     return MX_OK;

@@ -293,6 +293,64 @@ def test_mid_shape_every_output(elem):
                      "mid %s %s every output" % (elem, out_dtype))
 
 
+# one size or more for every tile shape the product chooses from, at the edges
+# of its tiles: rows and columns one past and one short of a tile, fewer K
+# steps than waves share out, and a step count no wave count divides
+@pytest.mark.parametrize("elem", ELEMS)
+@pytest.mark.parametrize("M,N,K", [
+    (1, 16, 256), (16, 496, 1280), (17, 528, 2816),        # 16 x 32 and 32 x 32 tiles, K split
+    (16, 6144, 4096), (31, 2064, 2304),
+    (33, 10256, 1280), (65, 4112, 768),                    # 32 x 64
+    (127, 6160, 2304), (1000, 784, 2304),                  # 64 x 64
+    (61, 20496, 768), (257, 6128, 1280), (2305, 784, 1024),  # ring, 64 x 128
+    (1000, 8208, 512), (1537, 2064, 3328),                 # ring, 128 x 128
+])
+def test_tile_shapes_every_output(elem, M, N, K):
+    rng = np.random.default_rng(M + 3 * N + 5 * K + len(elem))
+    ac, as_ = random_operand(M, K, elem, rng)
+    bc, bs = random_operand(N, K, elem, rng)
+    gain = torch.from_numpy(rng.standard_normal(N).astype(np.float32)).to(torch.bfloat16)
+    rows = tile_sample(M, tile=16, lead=2, tail=2, extra=4, seed=M)
+    want, mag = oracle_product(ac[rows], as_[rows], bc, bs, K, elem)
+    t = [dev_u8(v) for v in (ac, as_, bc, bs)]
+    gf = gain.double().numpy()
+    ri = torch.from_numpy(rows).to(DEV)
+    for out_dtype in (torch.float32, torch.bfloat16):
+        for g in (None, gain.to(DEV)):
+            # a store past the matrix shows in the 64 elements after it
+            buf = torch.full((M * N + 64,), 7.0, dtype=out_dtype, device=DEV)
+            h = buf[:M * N].view(M, N)
+            mxnorm.mx_matmul_fwd(*t, K, elem=elem, out_dtype=out_dtype, out=h, b_gain=g)
+            assert (buf[M * N:] == 7.0).all()
+            assert torch.isfinite(h).all()
+            got = h[ri].float().cpu().numpy().astype(np.float64)
+            f = 1.0 if g is None else gf
+            # the gain's product rounds once more in float32
+            extra = 0.0 if g is None else 2.0 ** -23 * np.abs(want * f)
+            assert_close(got, want * f, mag * np.abs(f) + 2.0 ** 9 * extra, out_dtype == torch.bfloat16,
+                         "shape %s %dx%dx%d %s" % (elem, M, N, K, out_dtype))
+
+
+@pytest.mark.parametrize("elem", ELEMS)
+def test_whole_rounds_and_smaller_tiles(elem):
+    # 17 x 17 cells of 256 x 256: one round of 256 on 256 compute units, and 33
+    # cells (the last row and column 10 and 16 wide) in a second launch of
+    # smaller tiles
+    M, N, K = 4106, 4112, 2048
+    rng = np.random.default_rng(71 + len(elem))
+    ac, as_ = random_operand(M, K, elem, rng)
+    bc, bs = random_operand(N, K, elem, rng)
+    buf = torch.full((M * N + 64,), 7.0, device=DEV)
+    h = buf[:M * N].view(M, N)
+    mxnorm.mx_matmul_fwd(dev_u8(ac), dev_u8(as_), dev_u8(bc), dev_u8(bs), K, elem=elem,
+                         out_dtype=torch.float32, out=h)
+    rows = tile_sample(M, lead=17)
+    got = h[torch.from_numpy(rows).to(DEV)].cpu().numpy().astype(np.float64)
+    assert (buf[M * N:] == 7.0).all() and torch.isfinite(h).all()
+    want, mag = oracle_product(ac[rows], as_[rows], bc, bs, K, elem)
+    assert_close(got, want, mag, False, "tail %s" % elem)
+
+
 def test_mxnorm_linear_forward_at_qkv_shape():
     # the benchmarked MXNormLinear forward: MXNorm of the Llama-3-8B
     # activations [32768, 4096] (outlier channels), then the product with
