@@ -278,6 +278,42 @@ mx_status mxnorm_ste_bwd_noalloc(const void *x, const void *grad_z, const void *
                                  void *grad_x, float *grad_gamma, hipStream_t stream);
 
 /*
+ * The MXNormLinear forward (Sec. 3.7 eq. (mx-matmul); the implementation
+ * appendix's mx_norm_linear_forward) as one call: mxnorm_mx_fwd of x [T, d],
+ * then mx_matmul_fwd with a weight cast once by mx_cast_fwd (codes and scales
+ * [N, .]).  Same arguments, arithmetic, outputs and errors as the two calls;
+ * out [T, N] in out_dtype, rho float [T] or NULL.  The activation codes and
+ * scales live in `workspace`: caller-owned device memory of
+ * mxnorm_linear_fwd_workspace_bytes() bytes, 256-byte aligned, overwritten.
+ */
+size_t mxnorm_linear_fwd_workspace_bytes(int64_t T, int64_t d, int block, int elem);
+mx_status mxnorm_linear_fwd(const void *x, int64_t T, int64_t d, const uint8_t *w_codes,
+                            const uint8_t *w_scales, int64_t N, int block, int elem, int p,
+                            float coef, float eps, int scale_mode, int out_dtype, void *out,
+                            float *rho, void *workspace, size_t workspace_bytes,
+                            hipStream_t stream);
+
+/*
+ * The MXNormLinear backward (Sec. 3.7; the implementation appendix's
+ * mx_norm_linear_backward) as one call:
+ *   grad_Z = MXCast(grad_H) MXCast_N(W)                    (bf16)
+ *   grad_X, grad_gamma = mxnorm_ste_bwd(X, grad_Z, gamma, rho~)
+ *   grad_W = (MXCast(grad_H^T) MXCast(rho~ X)^T) . gamma   (float32)
+ * grad_h: bf16 [T, N]; x: bf16 [T, d]; rho: float [T]; gamma: bf16 [d] or
+ * NULL; w: bf16 [N, d]; grad_x [T, d] in out_dtype, grad_gamma float [d],
+ * grad_w float [N, d].  RCEIL scales.  Values and errors are those of
+ * mx_cast_fwd, mx_cast_t_fwd, mx_matmul_fwd and mxnorm_ste_bwd called one by
+ * one.  `workspace`: caller-owned device memory of
+ * mxnorm_linear_bwd_workspace_bytes() bytes, 256-byte aligned, overwritten.
+ */
+size_t mxnorm_linear_bwd_workspace_bytes(int64_t T, int64_t N, int64_t d, int elem);
+mx_status mxnorm_linear_bwd(const void *grad_h, const void *x, const float *rho,
+                            const void *gamma, const void *w, int64_t T, int64_t N, int64_t d,
+                            int block, int elem, int out_dtype, void *grad_x, float *grad_gamma,
+                            float *grad_w, void *workspace, size_t workspace_bytes,
+                            hipStream_t stream);
+
+/*
  * Default NVFP4 tensor decode scales: an output bound divided by 6 * 448, so
  * the bound maps to the largest E2M1 x E4M3 magnitude.  MXNorm: Lemma 2's
  * bound K^(1/p) / coef (K = d / block; coef <= 0 selects the table value);

@@ -60,6 +60,12 @@ def load():
         "mxnorm_ste_bwd": (I, [P, P, P, P, I64, I64, I, P, P, P, ctypes.c_size_t, P]),
         "mxnorm_ste_bwd_noalloc_max_workspace": (ctypes.c_size_t, []),
         "mxnorm_ste_bwd_noalloc": (I, [P, P, P, P, I64, I64, I, P, P, P]),
+        "mxnorm_linear_fwd_workspace_bytes": (ctypes.c_size_t, [I64, I64, I, I]),
+        "mxnorm_linear_fwd": (I, [P, I64, I64, P, P, I64, I, I, I, F, F, I, I, P, P, P,
+                                  ctypes.c_size_t, P]),
+        "mxnorm_linear_bwd_workspace_bytes": (ctypes.c_size_t, [I64, I64, I64, I]),
+        "mxnorm_linear_bwd": (I, [P, P, P, P, P, I64, I64, I64, I, I, I, P, P, P, P,
+                                  ctypes.c_size_t, P]),
         "mxnorm_default_global_scale": (F, [I64, I, I, F]),
         "rmsnorm_default_global_scale": (F, [I64, F]),
         "mxnorm_coef": (F, [I, I]),
@@ -84,11 +90,13 @@ def _check(status):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(device):
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    # the handle of torch.cuda.current_stream(device), without building the
+    # Stream object around it (1.5 us a call)
+    return torch._C._cuda_getCurrentRawStream(device.index)
 
 
 def _input(x):
@@ -304,10 +312,21 @@ def mxnorm_linear_fwd(x, w_codes, w_scales, block=32, elem="e4m3", p=2, coef=0.0
     """The MXNormLinear forward H = MXNorm(X) MXCast(W gamma)^T (Sec. 3.7):
     MXNorm of the activations, then the MX matmul with a weight cast once by
     mx_cast_fwd(W, gamma).  Returns (H, rho~)."""
-    codes, scales, rho = mxnorm_mx_fwd(x, block=block, elem=elem, p=p, coef=coef, eps=eps,
-                                       scale_mode=scale_mode)
-    h = mx_matmul_fwd(codes, scales, w_codes, w_scales, x.shape[1], block=block, elem=elem,
-                      out_dtype=out_dtype)
+    T, d = _input(x)
+    _mx_out_shapes(T, d, block, elem)
+    mode = SCALE_MODES[scale_mode]
+    if out_dtype not in OUT_DTYPES:
+        raise ValueError("elem must be 'e4m3' or 'e2m1', out_dtype float32 or bfloat16")
+    N = _mx_operand(w_codes, w_scales, d, block, elem, "B")
+    lib, e = load(), ELEMS[elem]
+    h = torch.empty((T, N), dtype=out_dtype, device=x.device)
+    rho = torch.empty((T,), dtype=torch.float32, device=x.device)
+    ws_bytes = lib.mxnorm_linear_fwd_workspace_bytes(T, d, block, e)
+    ws = torch.empty((ws_bytes,), dtype=torch.uint8, device=x.device)
+    _check(lib.mxnorm_linear_fwd(x.data_ptr(), T, d, w_codes.data_ptr(), w_scales.data_ptr(), N,
+                                 block, e, p, coef, eps, mode, OUT_DTYPES[out_dtype],
+                                 h.data_ptr(), rho.data_ptr(), ws.data_ptr(), ws_bytes,
+                                 _stream(x.device)))
     return h, rho
 
 
@@ -402,19 +421,36 @@ def mxnorm_linear_bwd(grad_h, x, rho, gamma, w, block=32, elem="e4m3",
     grad_h bf16 [T, N], x bf16 [T, d], rho float32 [T], gamma bf16 [d],
     w bf16 [N, d].  Returns (grad_x, grad_gamma float32 [d], grad_w float32
     [N, d])."""
-    T, N = grad_h.shape
+    T, N = _input(grad_h)
+    if _input(x)[0] != T:
+        raise ValueError("x must have grad_h's rows")
     d = x.shape[1]
     if w.shape != (N, d):
         raise ValueError("w must be [N, d]")
-    gh_c, gh_s = mx_cast_fwd(grad_h, None, block=block, elem=elem)
-    wt_c, wt_s = mx_cast_t_fwd(w, None, block=block, elem=elem)
-    grad_z = mx_matmul_fwd(gh_c, gh_s, wt_c, wt_s, N, block=block, elem=elem,
-                           out_dtype=torch.bfloat16)
-    grad_x, grad_gamma = mxnorm_ste_bwd(x, grad_z, gamma, rho, out_dtype=grad_x_dtype)
-    ght_c, ght_s = mx_cast_t_fwd(grad_h, None, block=block, elem=elem)
-    xt_c, xt_s = mx_cast_t_fwd(x, rho, block=block, elem=elem)
-    grad_w = mx_matmul_fwd(ght_c, ght_s, xt_c, xt_s, T, block=block, elem=elem,
-                           out_dtype=torch.float32, b_gain=gamma)
+    _input(w)
+    if block not in (16, 32, 64) or elem not in ELEMS:
+        raise ValueError("block must be 16, 32 or 64 and elem 'e4m3' or 'e2m1'")
+    if x.device != grad_h.device or w.device != grad_h.device:
+        raise ValueError("grad_h, x and w must be on one device")
+    if rho.dtype != torch.float32 or rho.shape != (T,) or rho.device != x.device \
+            or not rho.is_contiguous():
+        raise ValueError("rho must be a contiguous float32 [T] tensor on x's device")
+    if gamma is not None:
+        _gamma(gamma, x)
+        if not gamma.is_contiguous():
+            raise ValueError("gamma must be contiguous")
+    if grad_x_dtype not in OUT_DTYPES:
+        raise ValueError("out_dtype must be float32 or bfloat16")
+    lib, e = load(), ELEMS[elem]
+    grad_x = torch.empty((T, d), dtype=grad_x_dtype, device=x.device)
+    grad_gamma = torch.empty((d,), dtype=torch.float32, device=x.device)
+    grad_w = torch.empty((N, d), dtype=torch.float32, device=x.device)
+    ws_bytes = lib.mxnorm_linear_bwd_workspace_bytes(T, N, d, e)
+    ws = torch.empty((ws_bytes,), dtype=torch.uint8, device=x.device)
+    _check(lib.mxnorm_linear_bwd(grad_h.data_ptr(), x.data_ptr(), rho.data_ptr(), _ptr(gamma),
+                                 w.data_ptr(), T, N, d, block, e, OUT_DTYPES[grad_x_dtype],
+                                 grad_x.data_ptr(), grad_gamma.data_ptr(), grad_w.data_ptr(),
+                                 ws.data_ptr(), ws_bytes, _stream(x.device)))
     return grad_x, grad_gamma, grad_w
 
 

@@ -314,3 +314,30 @@ def test_postround_validation():
     assert lib.mxnorm_postround_mx_fwd(A16, 4, 64, 32, 0, -1.0, 0, OUT, OUT, None, None) == 1
     assert lib.mxnorm_postround_mx_fwd(A16, 4, 64, 32, 0, 1e-6, 7, OUT, OUT, None, None) == 1
     assert lib.mxnorm_postround_mx_fwd(None, 0, 64, 32, 0, 1e-6, 0, None, None, None, None) == 0
+
+
+def test_linear_entries_reject_bad_arguments():
+    # the composed forward and backward refuse what their parts refuse, and a
+    # missing, small or misaligned workspace, before any launch
+    lib = mxnorm.load()
+    W = ctypes.c_void_p(0x100000)                    # 256-byte aligned
+    n = lib.mxnorm_linear_fwd_workspace_bytes(8, 1024, 32, 0)
+    assert n >= 8 * 1024 + 8 * 32
+    f = lib.mxnorm_linear_fwd
+    ok = [A16, 8, 1024, A16, A16, 64, 32, 0, 2, 0.0, 1e-6, 0, 0, A16, A16, W, n, None]
+    bad = lambda i, v: ok[:i] + [v] + ok[i + 1:]
+    assert f(*bad(15, None)) == 1 and f(*bad(16, n - 1)) == 1
+    assert f(*bad(15, ctypes.c_void_p(0x100010))) == 1
+    assert f(*bad(0, None)) == 1                                   # x NULL
+    assert f(*bad(8, 3)) == 1                                      # p
+    assert f(*bad(2, 1000)) == 1                                   # d % block
+    assert f(*bad(6, 48)) == 1                                     # block
+    n = lib.mxnorm_linear_bwd_workspace_bytes(256, 512, 256, 0)
+    assert n >= 2 * (256 * 512 + 512 * 256) + 2 * 256 * 256
+    assert lib.mxnorm_linear_bwd_workspace_bytes(256, 512, 256, 1) < n
+    b = lib.mxnorm_linear_bwd
+    ok = [A16, A16, A16, A16, A16, 256, 512, 256, 32, 0, 0, A16, A16, A16, W, n, None]
+    assert b(*bad(14, None)) == 1 and b(*bad(15, n - 1)) == 1
+    assert b(*bad(0, None)) == 1                                   # grad_h NULL
+    assert b(*bad(9, 2)) == 1                                      # elem
+    assert b(*bad(8, 48)) == 1                                     # block
