@@ -41,6 +41,7 @@
 #include "mx_gemm_ksplit.h"
 #include "mx_gemm_ring.h"
 #include "mxnorm.h"
+#include "products.h"
 #include "status.h"
 
 namespace mxg {
@@ -316,6 +317,128 @@ hipError_t launch(const Args &A, hipStream_t stream)
     return hipGetLastError();
 }
 
+// ------------------------------------------------- two products, one launch --
+
+// Two products in one persistent launch, so that the last, partly empty round
+// of one is filled with tiles of the other (the weight gradient's 384 tiles
+// on 256 compute units leave half of them idle for a round of 256 K steps).
+// A step takes about 2 us whether all compute units or half of them run, so
+// the fullest workgroup's load is the time.  Measured against the two
+// launches: 6144 x 4096 x 32768 with 32768 x 4096 x 6144 (E4M3) 1795 -> 1690
+// us, 6144 x 4096 x 4096 with 4096 x 4096 x 6144 142 -> 130 us (E2M1) and 216
+// -> 199 us (E4M3).
+// Workgroup b is of class b >= split; a workgroup of class c takes n[c][0]
+// tiles of product 0 (float output), then n[c][1] of product 1 (bf16 output).
+struct PairArgs {
+    Args p[2];
+    int split; // workgroups of class 0
+    int n[2][2];
+};
+
+// Product i's tile that is number j of workgroup b's share: the shares both
+// classes have in whole rounds over the grid, the rest in rounds over the
+// class that has more.  Past the product's last tile: -1.
+__device__ __forceinline__ int pair_tile(const PairArgs &W, int i, int j, int b, int grid)
+{
+    const int c = b >= W.split;
+    const int both = min(W.n[0][i], W.n[1][i]);
+    const int first = c ? W.split : 0, size = c ? grid - W.split : W.split;
+    const int v = j < both ? j * grid + b : both * grid + (j - both) * size + (b - first);
+    return j < W.n[c][i] && v < W.p[i].cells ? v : -1;
+}
+
+template <int ELEM> __global__ void __launch_bounds__(NT) mx_gemm_pair_kernel(PairArgs W)
+{
+    constexpr int SB = Op<ELEM>::SB;
+    constexpr int STAGE = Op<ELEM>::STAGE;
+    __shared__ __attribute__((aligned(16))) uint8_t lds[2 * STAGE];
+
+    const int tid = threadIdx.x;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6); // wave-uniform
+    const int l = tid & 63;
+    const int g = l >> 4, qd = l & 15;
+    const int wm = (w & 1) * WTM, wn = (w >> 1) * WTN;
+    const int b = blockIdx.x, grid = gridDim.x;
+
+    LDS_AS uint8_t *st0 = (LDS_AS uint8_t *)lds;
+    const uint32_t st0_addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)st0);
+    const FragBase ba = frag_base<ELEM>(0, (BM + BN) * KB, wm, qd, g);
+    const FragBase bb = frag_base<ELEM>(BM * KB, (BM + BN) * KB + BM * SB, wn, qd, g);
+
+    // tile number j of product i, and the one after it
+    int i = 0, j = 0, v = pair_tile(W, 0, 0, b, grid);
+    if (v < 0) {
+        i = 1;
+        v = pair_tile(W, 1, 0, b, grid);
+        if (v < 0)
+            return;
+    }
+    int64_t m0, n0;
+    tile_of(W.p[i], BM, BN, v, m0, n0);
+    Rows<ELEM> R = lane_rows<ELEM>(W.p[i], m0, n0, w, l);
+    const uint8_t *ta = W.p[i].a + m0 * W.p[i].rb, *tb = W.p[i].b + n0 * W.p[i].rb;
+    const uint8_t *tsa = W.p[i].as + m0 * W.p[i].rs, *tsb = W.p[i].bs + n0 * W.p[i].rs;
+
+    // the pipeline of mx_gemm_kernel
+    issue_step<ELEM>(ta, tb, tsa, tsb, R, 0, st0_addr, w);
+    int stores = 0; // stores of the previous tile, if it lies inside its H
+    for (int gs = 0;;) {
+        v4f acc[FN][FM];
+#pragma unroll
+        for (int n = 0; n < FN; ++n)
+#pragma unroll
+            for (int m = 0; m < FM; ++m)
+                acc[n][m] = v4f{0.f, 0.f, 0.f, 0.f};
+        int ni = i, nj = j + 1, nv = pair_tile(W, i, nj, b, grid);
+        if (nv < 0 && i == 0) {
+            ni = 1;
+            nj = 0;
+            nv = pair_tile(W, 1, 0, b, grid);
+        }
+        int64_t m1 = 0, n1 = 0;
+        const int steps = W.p[i].steps;
+        for (int s = 0; s < steps; ++s, ++gs) {
+            const int cur = gs & 1;
+            if (s == 0 && stores == kTileStores<MX_OUT_F32, FM, FN>)
+                wait_vmcnt<kTileStores<MX_OUT_F32, FM, FN>>();
+            else if (s == 0 && stores == kTileStores<MX_OUT_BF16, FM, FN>)
+                wait_vmcnt<kTileStores<MX_OUT_BF16, FM, FN>>();
+            else
+                wait_vmcnt<0>();
+            barrier();
+            const uint32_t nxt = st0_addr + (cur ^ 1) * STAGE;
+            if (s + 1 < steps) {
+                issue_step<ELEM>(ta, tb, tsa, tsb, R, s + 1, nxt, w);
+            } else if (nv >= 0) {
+                const Args &A = W.p[ni];
+                tile_of(A, BM, BN, nv, m1, n1);
+                R = lane_rows<ELEM>(A, m1, n1, w, l);
+                ta = A.a + m1 * A.rb;
+                tb = A.b + n1 * A.rb;
+                tsa = A.as + m1 * A.rs;
+                tsb = A.bs + n1 * A.rs;
+                issue_step<ELEM>(ta, tb, tsa, tsb, R, 0, nxt, w);
+            }
+            step_products<ELEM>(acc, st0 + cur * STAGE, ba, bb);
+        }
+        const bool full = m0 + BM <= W.p[i].M && n0 + BN <= W.p[i].N;
+        if (i == 0) {
+            store_tile<MX_OUT_F32, FM, FN>(W.p[0], acc, m0, n0, wm, wn, g, qd);
+            stores = full ? kTileStores<MX_OUT_F32, FM, FN> : 0;
+        } else {
+            store_tile<MX_OUT_BF16, FM, FN>(W.p[1], acc, m0, n0, wm, wn, g, qd);
+            stores = full ? kTileStores<MX_OUT_BF16, FM, FN> : 0;
+        }
+        if (nv < 0)
+            break;
+        i = ni;
+        j = nj;
+        v = nv;
+        m0 = m1;
+        n0 = n1;
+    }
+}
+
 // ------------------------------------------------------- choice of kernel --
 
 // Ring tiles: 4 waves, two workgroups per compute unit.
@@ -413,6 +536,90 @@ template <int ELEM, int OUT> hipError_t multiply(Args A, hipStream_t stream)
     return launch_shape<ELEM, OUT>(best, A, stream);
 }
 
+// The cheapest way `multiply` finds for one product, in us.
+inline double product_cost(const Args &A)
+{
+    const int cus = A.grid_max;
+    double cost = launch_cost(0, 1, A.M, A.N, A.steps, cus);
+    for (int s = 1; s < S_COUNT; ++s)
+        cost = std::min(cost, launch_cost(s, 1, A.M, A.N, A.steps, cus));
+    const int64_t cells = ((A.M + BM - 1) / BM) * ((A.N + BN - 1) / BN);
+    const int64_t whole = cells / cus * cus, left = cells - whole;
+    if (whole && left)
+        for (int s = 0; s < S_256x256; ++s)
+            cost = std::min(cost, launch_cost(S_256x256, whole, BM, BN, A.steps, cus) +
+                                      launch_cost(s, left, BM, BN, A.steps, cus));
+    return cost;
+}
+
+// Shares of the two products' tiles for `cus` workgroups that make the
+// fullest workgroup's load, in steps, as small as two classes of workgroups
+// can: class 0 takes n0 tiles of product 0, class 1 takes n1 > n0, and both
+// fill what the load leaves with tiles of product 1.  A tile costs its K
+// steps and about two steps' time for its stores.  Returns the load, or 0 if
+// the products have too many tiles to search.
+inline int64_t pair_plan(PairArgs &W, int cus)
+{
+    constexpr int kTileSteps = 2;
+    const int64_t g0 = W.p[0].cells, g1 = W.p[1].cells;
+    const int64_t c0 = W.p[0].steps + kTileSteps, c1 = W.p[1].steps + kTileSteps;
+    const int64_t q = g0 / cus;
+    if (q > 16 || g1 / cus > 4096)
+        return 0;
+    const int64_t lower = (g0 * c0 + g1 * c1 + cus - 1) / cus;
+    int64_t best = 0;
+    // the load of some workgroup is a * c0 + b * c1: for each a and pair of
+    // shares, the smallest such load that holds both products
+    for (int64_t lo = 0; lo <= q; ++lo)
+        for (int64_t hi = q + 1; hi <= q + 3; ++hi) {
+            // workgroups of class 1: the fewest that take the rest of product
+            // 0, in eights, so that a tile number keeps its workgroup's XCD
+            const int64_t k =
+                std::max<int64_t>(0, (g0 - lo * cus + (hi - lo) - 1) / (hi - lo) + 7) / 8 * 8;
+            if (k > cus)
+                continue;
+            for (int side = 0; side < 2; ++side) {
+                const int64_t a = side ? hi : lo;
+                int64_t b = lower > a * c0 ? (lower - a * c0 + c1 - 1) / c1 : 0;
+                for (int t = 0; t < 4; ++t, ++b) {
+                    const int64_t load = a * c0 + b * c1;
+                    if (load < (k ? hi : lo) * c0 || (best && load >= best))
+                        continue;
+                    const int64_t b0 = (load - lo * c0) / c1, b1 = k ? (load - hi * c0) / c1 : 0;
+                    if ((cus - k) * b0 + k * b1 < g1)
+                        continue;
+                    best = load;
+                    W.split = (int)(cus - k);
+                    W.n[0][0] = (int)lo;
+                    W.n[0][1] = (int)b0;
+                    W.n[1][0] = (int)hi;
+                    W.n[1][1] = (int)b1;
+                }
+            }
+        }
+    return best;
+}
+
+// Products 0 (float output) and 1 (bf16 output) on one stream: in one launch
+// where that beats the two by 3%.
+template <int ELEM> hipError_t multiply_pair(const Args &A0, const Args &A1, hipStream_t stream)
+{
+    PairArgs W;
+    W.p[0] = A0;
+    W.p[1] = A1;
+    set_tiles(W.p[0], BM, BN, 1024);
+    set_tiles(W.p[1], BM, BN, 1024);
+    const int cus = A0.grid_max;
+    const int64_t load = pair_plan(W, cus);
+    const double us = kCost[S_256x256].once + (double)load * kCost[S_256x256].step;
+    if (load && us < 0.97 * (product_cost(A0) + product_cost(A1))) {
+        hipLaunchKernelGGL((mx_gemm_pair_kernel<ELEM>), dim3((unsigned)cus), dim3(NT), 0, stream, W);
+        return hipGetLastError();
+    }
+    const hipError_t e = multiply<ELEM, MX_OUT_BF16>(A1, stream);
+    return e != hipSuccess ? e : multiply<ELEM, MX_OUT_F32>(A0, stream);
+}
+
 } // namespace mxg
 
 // host side -------------------------------------------------------------------
@@ -447,15 +654,13 @@ int compute_units(hipStream_t stream)
     return n;
 }
 
-} // namespace
-
-extern "C" {
-
-mx_status mx_matmul_fwd(const uint8_t *a_codes, const uint8_t *a_scales, const uint8_t *b_codes,
-                        const uint8_t *b_scales, int64_t M, int64_t N, int64_t K, int block,
-                        int elem, const void *b_gain, int out_dtype, void *out, hipStream_t stream)
+// The product's arguments, checked (see mx_matmul_fwd in the header); MX_OK
+// with M or N zero leaves `A` unset.
+mx_status matmul_args(mxg::Args &A, const uint8_t *a_codes, const uint8_t *a_scales,
+                      const uint8_t *b_codes, const uint8_t *b_scales, int64_t M, int64_t N,
+                      int64_t K, int block, int elem, const void *b_gain, int out_dtype, void *out,
+                      hipStream_t stream)
 {
-    mxk::clear_error();
     if (M < 0 || N < 0 || K <= 0)
         return mxk::fail(MX_EINVAL, "M and N must be >= 0 and K > 0");
     if (elem != MX_ELEM_E4M3 && elem != MX_ELEM_E2M1)
@@ -483,7 +688,6 @@ mx_status mx_matmul_fwd(const uint8_t *a_codes, const uint8_t *a_scales, const u
     const int64_t tm = (M + mxg::BM - 1) / mxg::BM, tn = (N + mxg::BN - 1) / mxg::BN;
     if (tm * tn > INT32_MAX / 2 || M > INT32_MAX || N > MX_MATMUL_MAX_N)
         return mxk::fail(MX_EUNSUPPORTED, "problem too large (N at most %d)", MX_MATMUL_MAX_N);
-    mxg::Args A;
     A.a = a_codes;
     A.as = a_scales;
     A.b = b_codes;
@@ -497,6 +701,23 @@ mx_status mx_matmul_fwd(const uint8_t *a_codes, const uint8_t *a_scales, const u
     A.steps = (int)(A.rb / mxg::KB);
     const int cus = compute_units(stream);
     A.grid_max = cus > 0 ? cus : 256;
+    return MX_OK;
+}
+
+} // namespace
+
+extern "C" {
+
+mx_status mx_matmul_fwd(const uint8_t *a_codes, const uint8_t *a_scales, const uint8_t *b_codes,
+                        const uint8_t *b_scales, int64_t M, int64_t N, int64_t K, int block,
+                        int elem, const void *b_gain, int out_dtype, void *out, hipStream_t stream)
+{
+    mxk::clear_error();
+    mxg::Args A;
+    const mx_status ok = matmul_args(A, a_codes, a_scales, b_codes, b_scales, M, N, K, block, elem,
+                                     b_gain, out_dtype, out, stream);
+    if (ok != MX_OK || M == 0 || N == 0)
+        return ok;
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipError_t e;
     if (elem == MX_ELEM_E4M3)
@@ -511,3 +732,23 @@ mx_status mx_matmul_fwd(const uint8_t *a_codes, const uint8_t *a_scales, const u
 }
 
 } // extern "C"
+
+namespace mxg {
+
+mx_status matmul_pair(const Product &f32, const Product &bf16, int elem, hipStream_t stream)
+{
+    Args A0, A1;
+    mx_status ok = matmul_args(A0, f32.a, f32.as, f32.b, f32.bs, f32.M, f32.N, f32.K, 32, elem,
+                               f32.gain, MX_OUT_F32, f32.out, stream);
+    if (ok == MX_OK)
+        ok = matmul_args(A1, bf16.a, bf16.as, bf16.b, bf16.bs, bf16.M, bf16.N, bf16.K, 32, elem,
+                         bf16.gain, MX_OUT_BF16, bf16.out, stream);
+    if (ok != MX_OK)
+        return ok;
+    const hipError_t e = elem == MX_ELEM_E4M3 ? multiply_pair<MX_ELEM_E4M3>(A0, A1, stream)
+                                              : multiply_pair<MX_ELEM_E2M1>(A0, A1, stream);
+    return e == hipSuccess ? MX_OK
+                           : mxk::fail(MX_EHIP, "kernel launch failed: %s", hipGetErrorString(e));
+}
+
+} // namespace mxg

@@ -283,6 +283,39 @@ def test_mxnorm_linear_backward(elem):
     assert rel < (0.10 if elem == "e4m3" else 0.30), rel
 
 
+@pytest.mark.parametrize("elem", ["e4m3", "e2m1"])
+@pytest.mark.parametrize("T,N,d", [
+    (256, 512, 256),        # small products, one launch each
+    (4096, 6144, 4096),     # 384 and 256 tiles: both products in one launch
+    (4352, 6400, 4128),     # 425 and 289 tiles, the last column of cells 32 wide
+    (8192, 2560, 2080),     # 90 and 288 tiles
+])
+def test_linear_backward_equals_its_parts(elem, T, N, d):
+    # the one-call backward against the library's own entry points called one
+    # by one.  Codes are the same bits; a product may add its K steps in
+    # another grouping, which moves float sums by at most 2^-22 of sum |ab|
+    # (a bf16 grad_Z then by one unit in rare elements).
+    g = torch.Generator(device=DEV)
+    g.manual_seed(T + N)
+    rnd = lambda *s: torch.randn(*s, generator=g, device=DEV).to(torch.bfloat16)
+    x, gh, w = rnd(T, d), 0.01 * rnd(T, N), 0.02 * rnd(N, d)
+    gam = 1 + 0.1 * rnd(d)
+    _, _, rho = mxnorm.mxnorm_mx_fwd(x, elem=elem)
+    gx, gg, gw = mxnorm.mxnorm_linear_bwd(gh, x, rho, gam, w, elem=elem, grad_x_dtype=torch.float32)
+    a, as_ = mxnorm.mx_cast_fwd(gh, None, elem=elem)
+    b, bs = mxnorm.mx_cast_t_fwd(w, None, elem=elem)
+    gz = mxnorm.mx_matmul_fwd(a, as_, b, bs, N, elem=elem, out_dtype=torch.bfloat16)
+    wx, wg = mxnorm.mxnorm_ste_bwd(x, gz, gam, rho, out_dtype=torch.float32)
+    a, as_ = mxnorm.mx_cast_t_fwd(gh, None, elem=elem)
+    b, bs = mxnorm.mx_cast_t_fwd(x, rho, elem=elem)
+    ww = mxnorm.mx_matmul_fwd(a, as_, b, bs, T, elem=elem, out_dtype=torch.float32, b_gain=gam)
+    torch.cuda.synchronize()
+    for name, got, want in (("grad_x", gx, wx), ("grad_gamma", gg, wg), ("grad_w", gw, ww)):
+        assert torch.isfinite(got).all(), name
+        err = float((got - want).norm() / want.norm())
+        assert err <= (1e-6 if name == "grad_w" else 1e-4), (name, err)
+
+
 def test_transpose_stream_reference_moves_the_bytes():
     # the column cast's stream reference (a bandwidth denominator) really
     # reads x and rho and writes the transposed bytes it claims to
