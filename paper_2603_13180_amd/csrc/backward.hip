@@ -27,6 +27,7 @@
 
 #include "mxnorm.h"
 #include "norm_cast.h"
+#include "products.h"
 #include "status.h"
 
 #pragma clang fp contract(off)
@@ -217,59 +218,46 @@ __device__ __forceinline__ void stage_tile(const TileLoad<COLS, NTH> &L, int tid
         rs[tid] = L.rv;
 }
 
-// Workgroup (tile_c, y) casts the 128 x COLS tile of x at columns COLS
-// tile_c and rows 128 (tile_r0 + y) (COLS = 256: 512-byte pieces of each x
-// row, 128-byte output pieces).  A tile is staged in LDS, then cast in passes of
-// 16 NW columns (NW waves): in pass h, lane 4 cc + b of wave w takes column
-// 16 NW h + 16 w + cc over rows 32 b .. 32 b + 31 (cast_block).  A column's
-// four scale bytes (blocks 0..3 of the tile) reach the quad's first lane
-// through DPP and go out as one dword when the tile is whole and R a
-// multiple of 128, else byte by byte.  One tile per workgroup with 512
-// threads was the fastest of the shapes measured on MI355X: at [32768, 4096]
-// 79 us against 83 (128-column tiles, 256 threads) and 89 (spans of four
-// 128-column tiles per workgroup, the next tile prefetched in registers, the
-// span's scale bytes gathered in LDS); at [32768, 28672] 626 against 632 us
-// (spans of 256-column tiles).
-template <bool FP4, int COLS, int NTH>
-__global__ void __launch_bounds__(NTH) cast_t_kernel(CastTArgs A)
+// Tile v of nc x nr column and row tiles.  order 0: dispatch order, the column
+// tiles of one row band after another.  order 1 (wide matrices): workgroups
+// are dispatched round robin over the 8 XCDs; renumbered so that each XCD
+// runs a contiguous range of a sequence that takes groups of 64 row tiles,
+// column tile by column tile.  The 32 workgroups an XCD runs at once then
+// write 4 KB runs of 256 output rows, where the dispatch order wrote 128-byte
+// pieces of thousands (MI355X, [32768, 28672]: 623 -> 544 us; [16384, 28672]
+// 308 -> 272; [32768, 14336] 286 -> 278; at 8192 columns and fewer the
+// dispatch order is faster).
+__device__ __forceinline__ void cast_tile_of(int order, int64_t v, int64_t nc, int64_t nr,
+                                             int64_t &ct, int64_t &rt)
 {
-    using S = CtShape<COLS, NTH>;
-    constexpr int NW = NTH / 64;
-    static_assert(COLS % (16 * NW) == 0, "whole passes");
-    __shared__ __attribute__((aligned(16))) uint8_t tile[4 * S::BLKB];
-    __shared__ __attribute__((aligned(16))) float rs[CT_ROWS];
-    const int tid = threadIdx.x;
-    // Tile of this workgroup.  order 0: dispatch order, the column tiles of
-    // one row band after another.  order 1 (wide matrices): workgroups are
-    // dispatched round robin over the 8 XCDs; renumbered so that each XCD
-    // runs a contiguous range of a sequence that takes groups of 64 row
-    // tiles, column tile by column tile.  The 32 workgroups an XCD runs at
-    // once then write 4 KB runs of 256 output rows, where the dispatch order
-    // wrote 128-byte pieces of thousands (MI355X, [32768, 28672]: 623 ->
-    // 544 us; [16384, 28672] 308 -> 272; [32768, 14336] 286 -> 278; at 8192
-    // columns and fewer the dispatch order is faster).
-    int64_t ct = blockIdx.x, rt = blockIdx.y;
-    if (A.order) {
+    if (order) {
         constexpr int64_t GR = 64, NX = 8;
-        const int64_t nc = gridDim.x, nr = gridDim.y, nt = nc * nr;
-        const int64_t v = ct + rt * nc;
+        const int64_t nt = nc * nr;
         const int64_t xcd = v % NX, loc = v / NX, q = nt / NX, rem = nt % NX;
         const int64_t p = xcd < rem ? xcd * (q + 1) + loc : rem * (q + 1) + (xcd - rem) * q + loc;
         const int64_t g = p / (GR * nc), in = p - g * GR * nc;
         const int64_t gsz = min(GR, nr - g * GR);
         rt = g * GR + in % gsz;
         ct = in / gsz;
+    } else {
+        rt = v / nc;
+        ct = v - rt * nc;
     }
-    const int64_t c0 = ct * COLS;
+}
+
+// The columns of a staged tile, in passes of 16 NW columns (NW waves): in pass
+// h, lane 4 cc + b of wave w takes column 16 NW h + 16 w + cc over rows 32 b ..
+// 32 b + 31 (cast_block).  A column's four scale bytes (blocks 0..3 of the
+// tile) reach the quad's first lane through DPP and go out as one dword when
+// the tile is whole and R a multiple of 128, else byte by byte.
+template <bool FP4, int COLS, int NTH>
+__device__ __forceinline__ void cast_columns(const CastTArgs &A, const uint8_t *tile,
+                                             const float *rs, int64_t r0, int64_t c0, int tid)
+{
+    constexpr int NW = NTH / 64;
+    static_assert(COLS % (16 * NW) == 0, "whole passes");
     const int w = tid >> 6, lane = tid & 63;
     const int blk = lane & 3; // 32-row block this lane casts
-    const int64_t r0 = (A.tile_r0 + rt) * CT_ROWS;
-    {
-        TileLoad<COLS, NTH> L;
-        fetch_tile<COLS, NTH>(A, r0, c0, tid, L);
-        stage_tile<COLS, NTH>(L, tid, tile, rs);
-    }
-    lds_barrier();
     const int64_t rb = r0 + 32 * blk; // first row of this lane's block
     const bool whole = r0 + CT_ROWS <= A.R && (A.R & 127) == 0;
 #pragma unroll
@@ -296,6 +284,131 @@ __global__ void __launch_bounds__(NTH) cast_t_kernel(CastTArgs A)
             }
         }
     }
+}
+
+// Workgroup (tile_c, y) casts the 128 x COLS tile of x at columns COLS
+// tile_c and rows 128 (tile_r0 + y) (COLS = 256: 512-byte pieces of each x
+// row, 128-byte output pieces).  A tile is staged in LDS, then cast column by
+// column.  One tile per workgroup with 512
+// threads was the fastest of the shapes measured on MI355X: at [32768, 4096]
+// 79 us against 83 (128-column tiles, 256 threads) and 89 (spans of four
+// 128-column tiles per workgroup, the next tile prefetched in registers, the
+// span's scale bytes gathered in LDS); at [32768, 28672] 626 against 632 us
+// (spans of 256-column tiles).
+template <bool FP4, int COLS, int NTH>
+__global__ void __launch_bounds__(NTH) cast_t_kernel(CastTArgs A)
+{
+    using S = CtShape<COLS, NTH>;
+    __shared__ __attribute__((aligned(16))) uint8_t tile[4 * S::BLKB];
+    __shared__ __attribute__((aligned(16))) float rs[CT_ROWS];
+    const int tid = threadIdx.x;
+    int64_t ct = blockIdx.x, rt = blockIdx.y;
+    if (A.order)
+        cast_tile_of(1, ct + rt * gridDim.x, gridDim.x, gridDim.y, ct, rt);
+    const int64_t c0 = ct * COLS, r0 = (A.tile_r0 + rt) * CT_ROWS;
+    {
+        TileLoad<COLS, NTH> L;
+        fetch_tile<COLS, NTH>(A, r0, c0, tid, L);
+        stage_tile<COLS, NTH>(L, tid, tile, rs);
+    }
+    lds_barrier();
+    cast_columns<FP4, COLS, NTH>(A, tile, rs, r0, c0, tid);
+}
+
+// -------------------------------------------------- the backward's casts --
+
+// The row cast of a tile from the registers it was loaded into: thread t's
+// 16-byte chunk is a quarter of a 32-column block, so a block's absmax is two
+// quad permutes away, and a lane writes 8 (E4M3) or 4 (E2M1) code bytes, 32
+// lanes one row's 256 or 128.  The four blocks of 16 lanes gather their scale
+// bytes by two rotations and store them as one dword.  RCEIL scales (no clamp
+// is needed before the conversion); C a multiple of 128.
+template <bool FP4, int COLS, int NTH>
+__device__ __forceinline__ void cast_rows(const CastTArgs &A, uint8_t *codes, uint8_t *scales,
+                                          int64_t r0, int64_t c0, int tid,
+                                          const TileLoad<COLS, NTH> &L)
+{
+    using S = CtShape<COLS, NTH>;
+    const int ch = tid % S::CPR, rbase = tid / S::CPR;
+    const int64_t c = c0 + 8 * ch;
+#pragma unroll
+    for (int k = 0; k < S::NLD; ++k) {
+        const int64_t r = r0 + rbase + S::RPP * k;
+        const uint4 v = L.v[k];
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+        const float a = __uint_as_float(block_max<4>(chunk_absmax_bits(v)) << 16);
+        const uint32_t byte = e8m0_byte<FP4>(a, MX_SCALE_RCEIL);
+        const float scale = __uint_as_float(byte << 23);
+        const bool in = r < A.R && c < A.C;
+        if constexpr (!FP4) {
+            uint32_t lo = e4m3x4_hw(bf16_lo(w[0]), bf16_hi(w[0]), bf16_lo(w[1]), bf16_hi(w[1]), scale);
+            uint32_t hi = e4m3x4_hw(bf16_lo(w[2]), bf16_hi(w[2]), bf16_lo(w[3]), bf16_hi(w[3]), scale);
+            if (__builtin_amdgcn_ballot_w64(byte == 0xFFu)) { // rare: non-finite input
+                if (byte == 0xFFu) {
+                    lo = nan_codes_e4m3(w[0], w[1]);
+                    hi = nan_codes_e4m3(w[2], w[3]);
+                }
+            }
+            if (in)
+                *reinterpret_cast<uint2 *>(codes + r * A.C + c) = make_uint2(lo, hi);
+        } else {
+            uint32_t q = 0;
+            q = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(q, bf16_lo(w[0]), bf16_hi(w[0]), scale, 0);
+            q = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(q, bf16_lo(w[1]), bf16_hi(w[1]), scale, 1);
+            q = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(q, bf16_lo(w[2]), bf16_hi(w[2]), scale, 2);
+            q = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(q, bf16_lo(w[3]), bf16_hi(w[3]), scale, 3);
+            if (__builtin_amdgcn_ballot_w64(byte == 0xFFu)) {
+                if (byte == 0xFFu)
+                    q = 0x77777777u | sign_nibbles(v);
+            }
+            if (in)
+                *reinterpret_cast<uint32_t *>(codes + (r * A.C + c) / 2) = q;
+        }
+        uint32_t b4 = byte << (8 * ((tid >> 2) & 3));
+        b4 |= dpp_mov<0x124>(b4); // row_ror:4
+        b4 |= dpp_mov<0x128>(b4); // row_ror:8
+        if (in && (tid & 15) == 0)
+            *reinterpret_cast<uint32_t *>(scales + r * (A.C / 32) + c / 32) = b4;
+    }
+}
+
+// The backward's four casts in one launch: grad_H by rows and by columns from
+// one read of it, W and rho X by columns.  HBM bound at large sizes: 32768 x
+// 6144 x 4096 (E4M3) 298 us as four launches, 218 us here (5.9 TB/s); launch
+// and latency bound at small ones: 1024 x 2304 x 768 23 -> 9 us.  Workgroups start[j] .. start[j + 1]
+// - 1 take job j's tiles (starts are multiples of 8, so that a tile's number
+// keeps its XCD).
+struct CastJobs {
+    CastTArgs job[3];
+    uint8_t *row_codes, *row_scales; // job 0's row cast
+    int start[4];
+};
+
+template <bool FP4, int COLS, int NTH>
+__global__ void __launch_bounds__(NTH) cast_jobs_kernel(CastJobs J)
+{
+    using S = CtShape<COLS, NTH>;
+    __shared__ __attribute__((aligned(16))) uint8_t tile[4 * S::BLKB];
+    __shared__ __attribute__((aligned(16))) float rs[CT_ROWS];
+    const int tid = threadIdx.x, b = blockIdx.x;
+    const int j = b >= J.start[2] ? 2 : b >= J.start[1] ? 1 : 0;
+    const CastTArgs &A = J.job[j];
+    const int64_t nc = (A.C + COLS - 1) / COLS, nr = (A.R + CT_ROWS - 1) / CT_ROWS;
+    const int64_t v = b - J.start[j];
+    if (v >= nc * nr)
+        return;
+    int64_t ct, rt;
+    cast_tile_of(A.order, v, nc, nr, ct, rt);
+    const int64_t c0 = ct * COLS, r0 = rt * CT_ROWS;
+    {
+        TileLoad<COLS, NTH> L;
+        fetch_tile<COLS, NTH>(A, r0, c0, tid, L);
+        stage_tile<COLS, NTH>(L, tid, tile, rs);
+        if (j == 0)
+            cast_rows<FP4, COLS, NTH>(A, J.row_codes, J.row_scales, r0, c0, tid, L);
+    }
+    lds_barrier();
+    cast_columns<FP4, COLS, NTH>(A, tile, rs, r0, c0, tid);
 }
 
 // ------------------------------------------------------------ STE rows --
@@ -660,6 +773,11 @@ namespace {
 
 bool aligned(const void *p, uintptr_t a) { return ((uintptr_t)p & (a - 1)) == 0; }
 
+constexpr int kCols = 256, kThreads = 512; // the column cast's tile and workgroup
+
+// the tile order for C columns: by XCD ranges from 12288 on (see the kernel)
+int cast_order(int64_t C) { return (C + kCols - 1) / kCols >= 48 ? 1 : 0; }
+
 int64_t ste_workgroups(int64_t T) { return (T + mxb::ste_rpw(T) - 1) / mxb::ste_rpw(T); }
 
 // Device-resident workspace of mxnorm_ste_bwd_noalloc: the grad_gamma partial
@@ -751,11 +869,10 @@ mx_status mx_cast_t_fwd(const void *x, const float *rho, int64_t R, int64_t C, i
     A.mode = scale_mode;
     // one 128 x 256 tile per workgroup (see the kernel), at most 65535 row
     // tiles per launch
-    constexpr int kCols = 256, kThreads = 512;
     constexpr int64_t kMaxRowTiles = 65535;
     const int64_t col_tiles = (C + kCols - 1) / kCols;
     const int64_t row_tiles = (R + mxb::CT_ROWS - 1) / mxb::CT_ROWS;
-    A.order = col_tiles >= 48 ? 1 : 0; // from 12288 columns on (see the kernel)
+    A.order = cast_order(C);
     hipStream_t st = static_cast<hipStream_t>(stream);
     for (int64_t t0 = 0; t0 < row_tiles; t0 += kMaxRowTiles) {
         A.tile_r0 = t0;
@@ -867,3 +984,51 @@ mx_status mxnorm_ste_bwd_noalloc(const void *x, const void *grad_z, const void *
 }
 
 } // extern "C"
+
+namespace mxb {
+
+mx_status backward_casts(const void *grad_h, const void *x, const float *rho, const void *w,
+                         int64_t T, int64_t N, int64_t d, int elem, const BackwardCasts &o,
+                         hipStream_t stream)
+{
+    CastJobs J;
+    auto job = [](const void *m, const float *r, int64_t R, int64_t C, uint8_t *codes,
+                  uint8_t *scales) {
+        CastTArgs A;
+        A.x = static_cast<const uint16_t *>(m);
+        A.rho = r;
+        A.codes = codes;
+        A.scales = scales;
+        A.R = R;
+        A.C = C;
+        A.tile_r0 = 0;
+        A.mode = MX_SCALE_RCEIL;
+        A.order = cast_order(C);
+        return A;
+    };
+    J.job[0] = job(grad_h, nullptr, T, N, o.ght, o.ght_s);
+    J.job[1] = job(w, nullptr, N, d, o.wt, o.wt_s);
+    J.job[2] = job(x, rho, T, d, o.xt, o.xt_s);
+    J.row_codes = o.gh;
+    J.row_scales = o.gh_s;
+    int64_t at = 0;
+    for (int j = 0; j < 3; ++j) {
+        J.start[j] = (int)at;
+        const int64_t tiles = ((J.job[j].C + kCols - 1) / kCols) * ((J.job[j].R + CT_ROWS - 1) / CT_ROWS);
+        at += (tiles + 7) / 8 * 8;
+        if (at > INT32_MAX)
+            return mxk::fail(MX_EUNSUPPORTED, "too many tiles to cast in one launch");
+    }
+    J.start[3] = (int)at;
+    if (elem == MX_ELEM_E4M3)
+        hipLaunchKernelGGL((cast_jobs_kernel<false, kCols, kThreads>), dim3((unsigned)at),
+                           dim3(kThreads), 0, stream, J);
+    else
+        hipLaunchKernelGGL((cast_jobs_kernel<true, kCols, kThreads>), dim3((unsigned)at),
+                           dim3(kThreads), 0, stream, J);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? MX_OK
+                           : mxk::fail(MX_EHIP, "kernel launch failed: %s", hipGetErrorString(e));
+}
+
+} // namespace mxb

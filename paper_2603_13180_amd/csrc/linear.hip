@@ -127,18 +127,19 @@ mx_status mxnorm_linear_bwd(const void *grad_h, const void *x, const float *rho,
         return st;
     const BwdSpace s(workspace, T, N, d, elem);
     const int mode = MX_SCALE_RCEIL;
-    // Both products in one call where every part of the backward takes the
-    // sizes; else part by part, which reports what is wrong with them.
+    // One launch for the casts and one, where it pays, for both products, if
+    // every part of the backward takes these arguments; else part by part,
+    // which reports what is wrong with them.
     const int64_t kstep = elem == MX_ELEM_E2M1 ? 256 : 128;
-    const bool together = T > 0 && N > 0 && d > 0 && block == 32 && known(elem) && T % kstep == 0 &&
-                          N % kstep == 0 && d % 32 == 0;
-    // grad_Z = MXCast(grad_H) MXCast_N(W), both blocked along N
-    if ((st = mx_cast_fwd(grad_h, nullptr, T, N, block, elem, mode, s.gh, s.gh_s, stream)) != MX_OK ||
-        (st = mx_cast_t_fwd(w, nullptr, N, d, block, elem, mode, s.wt, s.wt_s, stream)) != MX_OK)
-        return st;
-    if (together) {
-        if ((st = mx_cast_t_fwd(grad_h, nullptr, T, N, block, elem, mode, s.ght, s.ght_s, stream)) != MX_OK ||
-            (st = mx_cast_t_fwd(x, rho, T, d, block, elem, mode, s.xt, s.xt_s, stream)) != MX_OK ||
+    auto at16 = [](const void *p) { return p && ((uintptr_t)p & 15) == 0; };
+    if (T > 0 && N > 0 && d > 0 && block == 32 && known(elem) && T % kstep == 0 && N % kstep == 0 &&
+        d % 32 == 0 && d <= MXNORM_MAX_D && T <= MX_MATMUL_MAX_K && N <= MX_MATMUL_MAX_K &&
+        N <= MXNORM_MAX_D && (out_dtype == MX_OUT_F32 || out_dtype == MX_OUT_BF16) && at16(grad_h) &&
+        at16(x) && at16(w) && at16(grad_x) && at16(grad_w) && (!gamma || at16(gamma)) && rho &&
+        ((uintptr_t)rho & 3) == 0) {
+        if ((st = mxb::backward_casts(grad_h, x, rho, w, T, N, d, elem,
+                                      {s.gh, s.gh_s, s.ght, s.ght_s, s.wt, s.wt_s, s.xt, s.xt_s},
+                                      stream)) != MX_OK ||
             (st = mxg::matmul_pair({s.ght, s.ght_s, s.xt, s.xt_s, N, d, T, gamma, grad_w},
                                    {s.gh, s.gh_s, s.wt, s.wt_s, T, d, N, nullptr, s.gz}, elem,
                                    stream)) != MX_OK)
@@ -146,6 +147,10 @@ mx_status mxnorm_linear_bwd(const void *grad_h, const void *x, const float *rho,
         return mxnorm_ste_bwd(x, s.gz, gamma, rho, T, d, out_dtype, grad_x, grad_gamma, s.ste,
                               s.ste_bytes, stream);
     }
+    // grad_Z = MXCast(grad_H) MXCast_N(W), both blocked along N
+    if ((st = mx_cast_fwd(grad_h, nullptr, T, N, block, elem, mode, s.gh, s.gh_s, stream)) != MX_OK ||
+        (st = mx_cast_t_fwd(w, nullptr, N, d, block, elem, mode, s.wt, s.wt_s, stream)) != MX_OK)
+        return st;
     if ((st = mx_matmul_fwd(s.gh, s.gh_s, s.wt, s.wt_s, T, d, N, block, elem, nullptr, MX_OUT_BF16,
                             s.gz, stream)) != MX_OK)
         return st;

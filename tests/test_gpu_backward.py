@@ -289,6 +289,7 @@ def test_mxnorm_linear_backward(elem):
     (4096, 6144, 4096),     # 384 and 256 tiles: both products in one launch
     (4352, 6400, 4128),     # 425 and 289 tiles, the last column of cells 32 wide
     (8192, 2560, 2080),     # 90 and 288 tiles
+    (1280, 12544, 544),     # grad_H's cast in XCD ranges, with a partial group
 ])
 def test_linear_backward_equals_its_parts(elem, T, N, d):
     # the one-call backward against the library's own entry points called one
@@ -313,6 +314,37 @@ def test_linear_backward_equals_its_parts(elem, T, N, d):
     for name, got, want in (("grad_x", gx, wx), ("grad_gamma", gg, wg), ("grad_w", gw, ww)):
         assert torch.isfinite(got).all(), name
         err = float((got - want).norm() / want.norm())
+        assert err <= (1e-6 if name == "grad_w" else 1e-4), (name, err)
+
+
+@pytest.mark.parametrize("elem", ["e4m3", "e2m1"])
+def test_linear_backward_special_values(elem):
+    # zero rows and columns, subnormals, an infinity and a NaN in grad_H: the
+    # one-call backward has the parts' NaNs, and their values elsewhere
+    T, N, d = 512, 768, 288
+    g = torch.Generator(device=DEV)
+    g.manual_seed(9)
+    rnd = lambda *s: torch.randn(*s, generator=g, device=DEV).to(torch.bfloat16)
+    x, gh, w, gam = rnd(T, d), rnd(T, N), rnd(N, d), 1 + 0.1 * rnd(d)
+    gh[7], gh[:, 33] = 0, 0
+    gh[64:96, 128:160] *= 2.0 ** -126
+    gh[3, 5], gh[200, 700] = float("nan"), float("-inf")
+    _, _, rho = mxnorm.mxnorm_mx_fwd(x, elem=elem)
+    gx, gg, gw = mxnorm.mxnorm_linear_bwd(gh, x, rho, gam, w, elem=elem, grad_x_dtype=torch.float32)
+    a, as_ = mxnorm.mx_cast_fwd(gh, None, elem=elem)
+    b, bs = mxnorm.mx_cast_t_fwd(w, None, elem=elem)
+    gz = mxnorm.mx_matmul_fwd(a, as_, b, bs, N, elem=elem, out_dtype=torch.bfloat16)
+    wx, _ = mxnorm.mxnorm_ste_bwd(x, gz, gam, rho, out_dtype=torch.float32)
+    a, as_ = mxnorm.mx_cast_t_fwd(gh, None, elem=elem)
+    b, bs = mxnorm.mx_cast_t_fwd(x, rho, elem=elem)
+    ww = mxnorm.mx_matmul_fwd(a, as_, b, bs, T, elem=elem, out_dtype=torch.float32, b_gain=gam)
+    torch.cuda.synchronize()
+    assert torch.isnan(gg).all()                 # rows 3 and 200 reach every column
+    for name, got, want in (("grad_x", gx, wx), ("grad_w", gw, ww)):
+        nan = torch.isnan(want)
+        assert nan.any() and not nan.all(), name
+        assert torch.equal(torch.isnan(got), nan), name
+        err = float((got - want)[~nan].norm() / want[~nan].norm())
         assert err <= (1e-6 if name == "grad_w" else 1e-4), (name, err)
 
 
