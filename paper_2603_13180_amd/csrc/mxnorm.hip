@@ -100,12 +100,26 @@ float table_coef(int block, int p)
 
 // Team size (lanes per row, 16 .. 512) and register chunks per lane (4 or 8).
 // The smallest team that holds the row in at most 8 chunks per lane gives the
-// most independent loads per lane; when that leaves fewer than kMinWaves
-// waves in the launch (too few rows to cover 256 compute units several times
-// over), wider teams with fewer chunks per lane are taken, up to 64 lanes.
+// most independent loads per lane.  Wider teams with fewer chunks per lane are
+// taken (times on MI355X, us)
+//  * up to 64 lanes when that leaves fewer than kMinWaves waves in the launch
+//    (too few rows to cover 256 compute units several times over);
+//  * up to 256 lanes for at most kFewRows rows, where one row's chain of
+//    load, statistic and cast is the time ([16, 4096] MXFP8 3.7 -> 2.9,
+//    [512, 4096] 4.5 -> 4.1; [1000, 2048] is faster at 64 lanes, 3.9 against
+//    4.3), and 512 where a lane still has 4 chunks ([100, 16384] 4.9 -> 4.5);
+//  * twice the lanes when all waves are resident at once, so that nothing
+//    overlaps a wave's loads with another's arithmetic, and lanes have more
+//    than 4 chunks: RMSNorm, whose statistic takes every element ([16384,
+//    2048] 20.6 -> 19.2 MXFP8, 20.8 -> 19.7 NVFP4; [16384, 768] 9.9 -> 9.3),
+//    and MXNorm with full lanes except to MXFP4 ([16384, 2048] 18.9 -> 18.4
+//    MXFP8, 18.5 -> 17.6 NVFP4, but 16.4 -> 17.3 MXFP4).  With more waves
+//    than fit, [65536, 2048], NVFP4 loses 7%.
 constexpr int64_t kMinWaves = 4096;
+constexpr int64_t kResidentWaves = 8192; // 8 per SIMD
+constexpr int64_t kFewRows = 512;
 
-void pick_team(int64_t T, int nc, int &TL, int &CPL)
+void pick_team(int64_t T, int nc, int kind, int fmt, int &TL, int &CPL)
 {
     static const int sizes[] = {16, 32, 64, 128, 256, 512};
     TL = 0;
@@ -121,6 +135,16 @@ void pick_team(int64_t T, int nc, int &TL, int &CPL)
     // widen short-of-waves launches while every lane keeps at least one chunk
     while (TL < 64 && T * TL / 64 < kMinWaves && nc >= 2 * TL)
         TL *= 2;
+    if (T <= kFewRows) {
+        while (TL < 256 && nc >= 2 * TL)
+            TL *= 2;
+        if (TL == 256 && nc >= 8 * TL)
+            TL = 512;
+    } else if (TL < 64 && nc > 4 * TL && T * TL / 64 <= kResidentWaves) {
+        const bool fp4 = fmt >= MX4_B16 && fmt <= MX4_B64;
+        if (kind == K_RMS || (kind == K_MXN && nc == 8 * TL && !fp4))
+            TL *= 2;
+    }
     CPL = (nc + TL - 1) / TL <= 4 ? 4 : 8;
 }
 
@@ -158,7 +182,7 @@ mx_status check_global_scale(float s_g)
 mx_status run(Args A, int fmt, int kind, hipStream_t stream)
 {
     int TL, CPL;
-    pick_team(A.T, A.nc, TL, CPL);
+    pick_team(A.T, A.nc, kind, fmt, TL, CPL);
     if (TL == 0)
         return fail(MX_EUNSUPPORTED, "no launch configuration for d = %d", A.d);
     if (A.T == 0)

@@ -439,19 +439,6 @@ norm_cast_kernel(Args A)
     // workgroup instead of one per block.  A zero reciprocal marks the scales
     // whose blocks take the exact slow path (den = 0 or den < 2^-90).
     __shared__ float2 den_tab[NV ? 128 : 1];
-    float six_sg = 0.0f, rcp_six_sg = 0.0f;
-    bool six_sg_ok = false;
-    if constexpr (NV) {
-        if (threadIdx.x < 127) {
-            const float den = e4m3_value(threadIdx.x) * A.s_g;
-            den_tab[threadIdx.x] = make_float2(den, den >= 0x1p-90f ? 1.0f / den : 0.0f);
-        }
-        six_sg = A.six_sg;
-        rcp_six_sg = A.rcp_six_sg;
-        six_sg_ok = six_sg >= 0x1p-90f;
-        lds_barrier();
-    }
-
     const int tid = threadIdx.x;
     const int team = tid / TL;
     const int l = tid - team * TL;
@@ -483,6 +470,21 @@ norm_cast_kernel(Args A)
         const __amdgpu_buffer_rsrc_t xr = buffer_rsrc(A.x + row0 * A.d, rows * (uint32_t)A.d * 2u);
         const __amdgpu_buffer_rsrc_t cr = buffer_rsrc(A.codes + row0 * dcode, rows * dcode);
         load_row<TL, CPL>(xr, (uint32_t)team * (uint32_t)A.d * 2u, A.nc, l, v);
+        float six_sg = 0.0f, rcp_six_sg = 0.0f;
+        bool six_sg_ok = false;
+        // the table is formed while the row's loads are in flight (RMSNorm
+        // with a gain at [16384, 2048]: 21.8 -> 20.8 us against forming it
+        // first)
+        if constexpr (NV) {
+            if (threadIdx.x < 127) {
+                const float den = e4m3_value(threadIdx.x) * A.s_g;
+                den_tab[threadIdx.x] = make_float2(den, den >= 0x1p-90f ? 1.0f / den : 0.0f);
+            }
+            six_sg = A.six_sg;
+            rcp_six_sg = A.rcp_six_sg;
+            six_sg_ok = six_sg >= 0x1p-90f;
+            lds_barrier();
+        }
         // where this team's codes start in the store region; chunks past the
         // row's end store nowhere (the hardware drops the access)
         const uint32_t code_row = (uint32_t)team * dcode;

@@ -109,6 +109,27 @@ def test_shapes(kind, T, d):
     check(kind, xb, gb if kind.startswith("rmsnorm") else None)
 
 
+# both sides of the row counts and widths at which the team size changes
+TEAM_EDGES = [(512, 1056), (513, 1056), (512, 2080), (2, 14368), (300, 16384),
+              (8192, 1056), (16384, 1024), (16387, 768)]
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("T,d", TEAM_EDGES)
+def test_team_size_edges(kind, T, d):
+    xb = synth.gaussian(T, d, seed=T * 3 + d, scale=1.2)
+    gb = synth.f32_to_bf16_bits(np.random.default_rng(d).uniform(0.5, 1.5, d).astype(np.float32))
+    gb = gb if kind.startswith("rmsnorm") else None
+    s_g = None
+    if "nvfp4" in kind:
+        s_g = sg_rmsnorm(d, gb) if gb is not None else sg_mxnorm(d, 2)
+    got = run_gpu(kind, xb, gb, s_g=s_g)
+    # the oracle is slow: the first and last rows, where a partial workgroup is
+    rows = np.r_[0:min(T, 128), max(0, T - 128):T] if T > 1024 else np.arange(T)
+    assert_parity(kind, tuple(t[rows] for t in got), run_oracle(kind, xb[rows], gb, s_g=s_g),
+                  "shape=%s" % (xb.shape,))
+
+
 @pytest.mark.parametrize("kind", ["mxnorm_mxfp8", "mxnorm_nvfp4"])
 @pytest.mark.parametrize("p", [1, 2])
 @pytest.mark.parametrize("eps", [0.0, 1e-6, 0.5])
