@@ -58,23 +58,37 @@ inline void set_tiles(Args &A, int bm, int bn, int group_rows)
     A.cells = A.tiles_m * A.tiles_n;
 }
 
-// Tile v of a launch: its first row and column.  Dispatch is round robin over
-// the XCDs (each with its own L2); v is renumbered so that each XCD runs a
-// contiguous range of the launch's tiles.
+// Cell number t of the launch, counted in the launch's order: its row and
+// column of cells.
+__device__ __forceinline__ void cell_of(const Args &A, int t, int &cm, int &cn)
+{
+    const int pid = A.pid0 + t;
+    const int in_group = A.group * A.tiles_n;
+    const int first_m = (pid / in_group) * A.group;
+    const int gsz = min(A.tiles_m - first_m, A.group);
+    cm = first_m + (pid % in_group) % gsz;
+    cn = (pid % in_group) / gsz;
+}
+
+// Dispatch is round robin over the XCDs (each with its own L2): tile v of G,
+// renumbered so that each XCD runs a contiguous range.
+__device__ __forceinline__ int xcd_range(int v, int G)
+{
+    const int xcd = v % NXCD, loc = v / NXCD;
+    const int q = G / NXCD, rem = G % NXCD;
+    return xcd < rem ? xcd * (q + 1) + loc : rem * (q + 1) + (xcd - rem) * q + loc;
+}
+
+// Tile v of a launch: its first row and column.
 __device__ __forceinline__ void tile_of(const Args &A, int bm, int bn, int v, int64_t &m0,
                                         int64_t &n0)
 {
     const int nsub = A.sub_m * A.sub_n;
-    const int G = A.cells * nsub;
-    const int xcd = v % NXCD, loc = v / NXCD;
-    const int q = G / NXCD, rem = G % NXCD;
-    const int t = xcd < rem ? xcd * (q + 1) + loc : rem * (q + 1) + (xcd - rem) * q + loc;
-    const int pid = A.pid0 + t / nsub, sub = t % nsub;
-    const int in_group = A.group * A.tiles_n;
-    const int first_m = (pid / in_group) * A.group;
-    const int gsz = min(A.tiles_m - first_m, A.group);
-    m0 = (int64_t)(first_m + (pid % in_group) % gsz) * A.cell_m + (sub % A.sub_m) * bm;
-    n0 = (int64_t)((pid % in_group) / gsz) * A.cell_n + (sub / A.sub_m) * bn;
+    const int t = xcd_range(v, A.cells * nsub), sub = t % nsub;
+    int cm, cn;
+    cell_of(A, t / nsub, cm, cn);
+    m0 = (int64_t)cm * A.cell_m + (sub % A.sub_m) * bm;
+    n0 = (int64_t)cn * A.cell_n + (sub / A.sub_m) * bn;
 }
 
 // Global -> LDS DMA loads: lane i of the wave reads gbase + off_i (gbase

@@ -53,6 +53,16 @@ constexpr int WTM = 128;   // wave tile along M
 constexpr int WTN = 64;    // wave tile along N
 constexpr int FM = WTM / 16, FN = WTN / 16;
 
+// Tile v of a launch whose cells are 256 x 256 (fewer divisions than tile_of:
+// they stand between two tiles' loads).
+__device__ __forceinline__ void whole_tile(const Args &A, int v, int64_t &m0, int64_t &n0)
+{
+    int cm, cn;
+    cell_of(A, xcd_range(v, A.cells), cm, cn);
+    m0 = (int64_t)cm * BM;
+    n0 = (int64_t)cn * BN;
+}
+
 template <int ELEM> struct Op {
     static constexpr int SB = kSB<ELEM>;
     static constexpr int STAGE = (BM + BN) * KB + (BM + BN) * SB;
@@ -254,7 +264,7 @@ __global__ void __launch_bounds__(NT) mx_gemm_kernel(Args A)
 
     int v = blockIdx.x;
     int64_t m0, n0;
-    tile_of(A, BM, BN, v, m0, n0);
+    whole_tile(A, v, m0, n0);
     Rows<ELEM> R = lane_rows<ELEM>(A, m0, n0, w, l);
 
     // Pipeline, one barrier per K step.  At the top of a step every wave has
@@ -291,7 +301,7 @@ __global__ void __launch_bounds__(NT) mx_gemm_kernel(Args A)
                 issue_step<ELEM>(A.a + m0 * A.rb, A.b + n0 * A.rb, A.as + m0 * A.rs,
                                  A.bs + n0 * A.rs, R, s + 1, nxt, w);
             } else if (nv < G) {
-                tile_of(A, BM, BN, nv, m1, n1);
+                whole_tile(A, nv, m1, n1);
                 R = lane_rows<ELEM>(A, m1, n1, w, l);
                 issue_step<ELEM>(A.a + m1 * A.rb, A.b + n1 * A.rb, A.as + m1 * A.rs,
                                  A.bs + n1 * A.rs, R, 0, nxt, w);
@@ -374,7 +384,7 @@ template <int ELEM> __global__ void __launch_bounds__(NT) mx_gemm_pair_kernel(Pa
             return;
     }
     int64_t m0, n0;
-    tile_of(W.p[i], BM, BN, v, m0, n0);
+    whole_tile(W.p[i], v, m0, n0);
     Rows<ELEM> R = lane_rows<ELEM>(W.p[i], m0, n0, w, l);
     const uint8_t *ta = W.p[i].a + m0 * W.p[i].rb, *tb = W.p[i].b + n0 * W.p[i].rb;
     const uint8_t *tsa = W.p[i].as + m0 * W.p[i].rs, *tsb = W.p[i].bs + n0 * W.p[i].rs;
@@ -411,7 +421,7 @@ template <int ELEM> __global__ void __launch_bounds__(NT) mx_gemm_pair_kernel(Pa
                 issue_step<ELEM>(ta, tb, tsa, tsb, R, s + 1, nxt, w);
             } else if (nv >= 0) {
                 const Args &A = W.p[ni];
-                tile_of(A, BM, BN, nv, m1, n1);
+                whole_tile(A, nv, m1, n1);
                 R = lane_rows<ELEM>(A, m1, n1, w, l);
                 ta = A.a + m1 * A.rb;
                 tb = A.b + n1 * A.rb;
