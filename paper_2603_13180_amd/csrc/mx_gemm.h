@@ -71,7 +71,9 @@ __device__ __forceinline__ void cell_of(const Args &A, int t, int &cm, int &cn)
 }
 
 // Dispatch is round robin over the XCDs (each with its own L2): tile v of G,
-// renumbered so that each XCD runs a contiguous range.
+// renumbered so that each XCD runs a contiguous range (256 x 256 tiles, E4M3,
+// against plain round robin: 32768 x 6144 x 4096 737 against 801 us, 16384 x
+// 28672 x 4096 1583 against 1715).
 __device__ __forceinline__ int xcd_range(int v, int G)
 {
     const int xcd = v % NXCD, loc = v / NXCD;
