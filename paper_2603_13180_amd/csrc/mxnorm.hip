@@ -33,6 +33,7 @@
 #include "mxnorm.h"
 #include "norm_cast.h"
 #include "status.h"
+#include "testing.h"
 
 #include <cmath>
 #include <mutex>
@@ -105,21 +106,32 @@ float table_coef(int block, int p)
 //  * up to 64 lanes when that leaves fewer than kMinWaves waves in the launch
 //    (too few rows to cover 256 compute units several times over);
 //  * up to 256 lanes for at most kFewRows rows, where one row's chain of
-//    load, statistic and cast is the time ([16, 4096] MXFP8 3.7 -> 2.9,
-//    [512, 4096] 4.5 -> 4.1; [1000, 2048] is faster at 64 lanes, 3.9 against
-//    4.3), and 512 where a lane still has 4 chunks ([100, 16384] 4.9 -> 4.5);
-//  * twice the lanes when all waves are resident at once, so that nothing
-//    overlaps a wave's loads with another's arithmetic, and lanes have more
-//    than 4 chunks: RMSNorm, whose statistic takes every element ([16384,
-//    2048] 20.6 -> 19.2 MXFP8, 20.8 -> 19.7 NVFP4; [16384, 768] 9.9 -> 9.3),
-//    and MXNorm with full lanes except to MXFP4 ([16384, 2048] 18.9 -> 18.4
-//    MXFP8, 18.5 -> 17.6 NVFP4, but 16.4 -> 17.3 MXFP4).  With more waves
-//    than fit, [65536, 2048], NVFP4 loses 7%.
+//    load, statistic and cast is the time, while a lane has more than 3
+//    chunks ([16, 4096] MXFP8 3.7 -> 2.9, [512, 4096] 4.5 -> 4.1): with 3 the
+//    wider lane has 2 of which half is idle ([400, 1536] MXFP8 3.4 -> 3.8,
+//    [512, 3072] 3.75 -> 4.0 with 256 lanes), with 2 the join through LDS
+//    eats the gain ([32, 1024] 2.73 -> 2.80).  From kFullRows rows on, where
+//    all compute units are busy, only if no chunk of the wider lanes is idle
+//    ([512, 4096] 1.1 times as fast, but [512, 5120] 3.80 -> 4.15, [400, 2560]
+//    3.24 -> 3.40).  Five chunks in a lane of 64 are left at that ([32, 2560]
+//    MXFP8 3.08 -> 3.18, [256, 2560] 3.25 -> 3.39).  NVFP4, whose arithmetic
+//    per chunk is longest, from 2 chunks on ([256, 3072] 1.3 times as fast
+//    with 256 lanes as with 64, [256, 1024] 1.02);
+//  * 512 for as few rows where a lane of 256 still has 8 chunks ([100, 16384]
+//    4.9 -> 4.5);
+//  * twice the lanes for RMSNorm with a gain, whose lanes do the most work per
+//    chunk, when its waves are resident at once, so that nothing overlaps a
+//    wave's loads with another's arithmetic, and at least kManyWaves of them
+//    ([16384, 2048] NVFP4 20.8 -> 19.7).  The chunk count per lane has to be
+//    even: else the wider lanes' last chunk is half idle ([14000, 1792] NVFP4
+//    4% slower, [16384, 1280] 7%).  Below kManyWaves, [8192, 2048] MXFP8 loses
+//    8%; with more waves than fit, [65536, 2048] NVFP4 loses 7%; without a
+//    gain, [12000, 2048] MXFP8 loses 7% and MXNorm 8%.
 constexpr int64_t kMinWaves = 4096;
-constexpr int64_t kResidentWaves = 8192; // 8 per SIMD
-constexpr int64_t kFewRows = 512;
+constexpr int64_t kManyWaves = 6000, kResidentWaves = 8192; // 8192: 8 per SIMD
+constexpr int64_t kFullRows = 257, kFewRows = 512;
 
-void pick_team(int64_t T, int nc, int kind, int fmt, int &TL, int &CPL)
+void pick_team(int64_t T, int nc, int kind, int fmt, bool gain, int &TL, int &CPL)
 {
     static const int sizes[] = {16, 32, 64, 128, 256, 512};
     TL = 0;
@@ -136,14 +148,19 @@ void pick_team(int64_t T, int nc, int kind, int fmt, int &TL, int &CPL)
     while (TL < 64 && T * TL / 64 < kMinWaves && nc >= 2 * TL)
         TL *= 2;
     if (T <= kFewRows) {
-        while (TL < 256 && nc >= 2 * TL)
+        auto wider = [&] {
+            if (fmt == NV4_B16)
+                return nc >= 2 * TL;
+            const bool five = TL == 64 && nc > 4 * TL && nc <= 5 * TL;
+            return nc > 3 * TL && !five && (T < kFullRows || nc % (2 * TL) == 0);
+        };
+        while (TL < 256 && wider())
             TL *= 2;
         if (TL == 256 && nc >= 8 * TL)
             TL = 512;
-    } else if (TL < 64 && nc > 4 * TL && T * TL / 64 <= kResidentWaves) {
-        const bool fp4 = fmt >= MX4_B16 && fmt <= MX4_B64;
-        if (kind == K_RMS || (kind == K_MXN && nc == 8 * TL && !fp4))
-            TL *= 2;
+    } else if (TL < 64 && nc > 4 * TL && kind == K_RMS && gain && (nc + TL - 1) / TL % 2 == 0 &&
+               T * TL / 64 >= kManyWaves && T * TL / 64 <= kResidentWaves) {
+        TL *= 2;
     }
     CPL = (nc + TL - 1) / TL <= 4 ? 4 : 8;
 }
@@ -182,7 +199,7 @@ mx_status check_global_scale(float s_g)
 mx_status run(Args A, int fmt, int kind, hipStream_t stream)
 {
     int TL, CPL;
-    pick_team(A.T, A.nc, kind, fmt, TL, CPL);
+    pick_team(A.T, A.nc, kind, fmt, A.gamma != nullptr, TL, CPL);
     if (TL == 0)
         return fail(MX_EUNSUPPORTED, "no launch configuration for d = %d", A.d);
     if (A.T == 0)
@@ -547,5 +564,12 @@ const char *mx_status_str(mx_status s)
 const char *mx_last_error(void) { return mxk::last_error(); }
 
 int mxnorm_abi_version(void) { return MXNORM_ABI_VERSION; }
+
+int mxt_norm_team(int64_t T, int64_t d, int kind, int fmt, int gain)
+{
+    int TL, CPL;
+    pick_team(T, (int)(d / 8), kind, fmt, gain != 0, TL, CPL);
+    return TL;
+}
 
 } // extern "C"

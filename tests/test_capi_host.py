@@ -341,3 +341,29 @@ def test_linear_entries_reject_bad_arguments():
     assert b(*bad(0, None)) == 1                                   # grad_h NULL
     assert b(*bad(9, 2)) == 1                                      # elem
     assert b(*bad(8, 48)) == 1                                     # block
+
+
+RMS, MXN, CAST, POST = 0, 1, 2, 3                     # kinds of mxt_norm_team
+MX8_B32, MX4_B32, NV4 = 1, 4, 6                       # and its formats
+
+
+@pytest.mark.parametrize("T,d,kind,fmt,gain,lanes", [
+    # at most 512 rows: wider teams while a lane has more than 3 chunks of 8
+    # columns (NVFP4: while it has 2), above 256 rows only without idle chunks
+    (16, 4096, MXN, MX8_B32, 0, 256), (512, 4096, POST, MX8_B32, 0, 256), (100, 16384, MXN, MX8_B32, 0, 512),
+    (400, 1536, MXN, MX8_B32, 0, 64), (512, 1536, CAST, MX4_B32, 0, 64), (32, 1024, RMS, MX8_B32, 1, 64),
+    (512, 3072, MXN, MX8_B32, 0, 128), (256, 1568, MXN, MX8_B32, 0, 128), (257, 1568, MXN, MX8_B32, 0, 64),
+    (256, 5120, CAST, MX8_B32, 1, 256), (512, 5120, RMS, MX8_B32, 0, 128), (400, 2560, MXN, MX8_B32, 0, 64),
+    (8, 2560, MXN, MX8_B32, 0, 64), (256, 2080, RMS, MX4_B32, 0, 64), (256, 2592, RMS, MX4_B32, 0, 128),
+    (256, 1024, MXN, NV4, 0, 128), (256, 3072, RMS, NV4, 1, 256),
+    # more rows: twice the lanes only for RMSNorm with a gain, an even number
+    # of chunks per lane and enough waves, all resident
+    (16384, 2048, RMS, NV4, 1, 64), (12000, 1536, RMS, MX8_B32, 1, 64), (24000, 768, RMS, MX8_B32, 1, 32),
+    (16384, 2048, RMS, NV4, 0, 32), (8192, 2048, RMS, MX8_B32, 0, 32), (16384, 1024, RMS, MX8_B32, 0, 16),
+    (16384, 2048, MXN, NV4, 0, 32), (8192, 2048, MXN, MX8_B32, 0, 32), (16384, 1024, MXN, MX8_B32, 0, 16),
+    (16384, 1792, RMS, NV4, 1, 32), (16384, 1280, RMS, MX8_B32, 1, 32), (8192, 2048, RMS, MX8_B32, 1, 32),
+    (30000, 640, RMS, MX4_B32, 1, 16), (16386, 2048, RMS, NV4, 1, 32), (65536, 2048, RMS, NV4, 1, 32),
+])
+def test_norm_team_widths(T, d, kind, fmt, gain, lanes):
+    # each width is the faster one measured at that size
+    assert mxnorm.load().mxt_norm_team(ctypes.c_int64(T), ctypes.c_int64(d), kind, fmt, gain) == lanes

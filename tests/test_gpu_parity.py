@@ -111,7 +111,9 @@ def test_shapes(kind, T, d):
 
 # both sides of the row counts and widths at which the team size changes
 TEAM_EDGES = [(512, 1056), (513, 1056), (512, 2080), (2, 14368), (300, 16384),
-              (8192, 1056), (16384, 1024), (16387, 768)]
+              (8192, 1056), (16384, 1024), (16387, 768),
+              (256, 1536), (256, 1568), (257, 1568), (512, 3072), (512, 3104),
+              (11999, 1536), (12000, 1536), (24000, 768)]
 
 
 @pytest.mark.parametrize("kind", KINDS)
