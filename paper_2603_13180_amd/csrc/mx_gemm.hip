@@ -43,6 +43,7 @@
 #include "mxnorm.h"
 #include "products.h"
 #include "status.h"
+#include "testing.h"
 
 namespace mxg {
 
@@ -489,6 +490,45 @@ inline double launch_cost(int shape, int64_t cells, int64_t cm, int64_t cn, int 
     return c.once + (double)rounds * (c.round + (double)steps * c.step);
 }
 
+// How one product is computed: the whole output in tiles of `shape`; or, where
+// that is at least 5% cheaper, its first `whole` cells of 256 x 256 (whole
+// rounds of them) in one launch and the cells left in tiles of `tail` in a
+// second.
+struct Plan {
+    int shape;
+    int whole, tail; // whole = 0: one launch
+    double us;
+};
+
+inline Plan plan_product(int64_t M, int64_t N, int steps, int cus)
+{
+    Plan P{S_256x256, 0, 0, launch_cost(S_256x256, 1, M, N, steps, cus)};
+    for (int s = 0; s < S_256x256; ++s) {
+        const double c = launch_cost(s, 1, M, N, steps, cus);
+        if (c < P.us) {
+            P.us = c;
+            P.shape = s;
+        }
+    }
+    const int64_t cells = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
+    const int64_t whole = cells / cus * cus, left = cells - whole;
+    if (whole && left) {
+        int tail = 0;
+        double tcost = launch_cost(0, left, BM, BN, steps, cus);
+        for (int s = 1; s < S_256x256; ++s) {
+            const double c = launch_cost(s, left, BM, BN, steps, cus);
+            if (c < tcost) {
+                tcost = c;
+                tail = s;
+            }
+        }
+        const double two = launch_cost(S_256x256, whole, BM, BN, steps, cus) + tcost;
+        if (two < 0.95 * P.us)
+            P = Plan{S_256x256, (int)whole, tail, two};
+    }
+    return P;
+}
+
 template <int ELEM, int OUT> hipError_t launch_shape(int shape, const Args &A, hipStream_t stream)
 {
     switch (shape) {
@@ -502,64 +542,27 @@ template <int ELEM, int OUT> hipError_t launch_shape(int shape, const Args &A, h
     }
 }
 
-// One shape for the whole output, the cheapest; or whole rounds of 256 x 256
-// tiles and a second launch of the cheapest smaller shape over the tiles
-// left, where that is at least 5% cheaper.
-template <int ELEM, int OUT> hipError_t multiply(Args A, hipStream_t stream)
+template <int ELEM, int OUT>
+hipError_t multiply_as(const Plan &P, Args A, hipStream_t stream)
 {
-    const int cus = A.grid_max;
-    int best = S_256x256;
-    double cost = launch_cost(best, 1, A.M, A.N, A.steps, cus);
-    for (int s = 0; s < S_256x256; ++s) {
-        const double c = launch_cost(s, 1, A.M, A.N, A.steps, cus);
-        if (c < cost) {
-            cost = c;
-            best = s;
-        }
-    }
-    set_tiles(A, BM, BN, 1024);
-    const int whole = A.cells / cus * cus, left = A.cells - whole;
-    if (whole && left) {
-        int tail = 0;
-        double tcost = launch_cost(0, left, BM, BN, A.steps, cus);
-        for (int s = 1; s < S_256x256; ++s) {
-            const double c = launch_cost(s, left, BM, BN, A.steps, cus);
-            if (c < tcost) {
-                tcost = c;
-                tail = s;
-            }
-        }
-        if (launch_cost(S_256x256, whole, BM, BN, A.steps, cus) + tcost < 0.95 * cost) {
-            A.cells = whole;
-            const hipError_t e = launch<ELEM, OUT>(A, stream);
-            if (e != hipSuccess)
-                return e;
-            A.pid0 = whole;
-            A.cells = left;
-            A.sub_m = BM / kCost[tail].bm;
-            A.sub_n = BN / kCost[tail].bn;
-            return launch_shape<ELEM, OUT>(tail, A, stream);
-        }
-    }
-    if (best != S_256x256)
-        set_tiles(A, kCost[best].bm, kCost[best].bn, 1024);
-    return launch_shape<ELEM, OUT>(best, A, stream);
+    set_tiles(A, kCost[P.shape].bm, kCost[P.shape].bn, 1024);
+    if (!P.whole)
+        return launch_shape<ELEM, OUT>(P.shape, A, stream);
+    const int left = A.cells - P.whole;
+    A.cells = P.whole;
+    const hipError_t e = launch<ELEM, OUT>(A, stream);
+    if (e != hipSuccess)
+        return e;
+    A.pid0 = P.whole;
+    A.cells = left;
+    A.sub_m = BM / kCost[P.tail].bm;
+    A.sub_n = BN / kCost[P.tail].bn;
+    return launch_shape<ELEM, OUT>(P.tail, A, stream);
 }
 
-// The cheapest way `multiply` finds for one product, in us.
-inline double product_cost(const Args &A)
+template <int ELEM, int OUT> hipError_t multiply(const Args &A, hipStream_t stream)
 {
-    const int cus = A.grid_max;
-    double cost = launch_cost(0, 1, A.M, A.N, A.steps, cus);
-    for (int s = 1; s < S_COUNT; ++s)
-        cost = std::min(cost, launch_cost(s, 1, A.M, A.N, A.steps, cus));
-    const int64_t cells = ((A.M + BM - 1) / BM) * ((A.N + BN - 1) / BN);
-    const int64_t whole = cells / cus * cus, left = cells - whole;
-    if (whole && left)
-        for (int s = 0; s < S_256x256; ++s)
-            cost = std::min(cost, launch_cost(S_256x256, whole, BM, BN, A.steps, cus) +
-                                      launch_cost(s, left, BM, BN, A.steps, cus));
-    return cost;
+    return multiply_as<ELEM, OUT>(plan_product(A.M, A.N, A.steps, A.grid_max), A, stream);
 }
 
 // Shares of the two products' tiles for `cus` workgroups that make the
@@ -610,48 +613,71 @@ inline int64_t pair_plan(PairArgs &W, int cus)
     return best;
 }
 
-// Products 0 (float output) and 1 (bf16 output) on one stream: in one launch
-// where that is 3% cheaper than one launch each, on 256 x 256 tiles shared out
-// by load or on 64 x 128 tiles that are all resident at once.
-template <int ELEM> hipError_t multiply_pair(const Args &A0, const Args &A1, hipStream_t stream)
+// How two products are computed: one launch each, or in one launch on 256 x
+// 256 tiles shared out by load or on 64 x 128 tiles that are all resident at
+// once, where that is 3% cheaper.
+enum PairMode { PAIR_APART, PAIR_LARGE, PAIR_SMALL };
+struct PairPlan {
+    int mode;
+    double apart, large, small; // us; large or small = apart: not possible
+    PairArgs W;
+    RingPair Q;
+};
+
+inline void plan_pair(PairPlan &P, const Args &A0, const Args &A1)
 {
     const int cus = A0.grid_max;
-    const double apart = product_cost(A0) + product_cost(A1);
-    PairArgs W;
-    W.p[0] = A0;
-    W.p[1] = A1;
-    set_tiles(W.p[0], BM, BN, 1024);
-    set_tiles(W.p[1], BM, BN, 1024);
-    const int64_t load = pair_plan(W, cus);
-    const double big = load ? kCost[S_256x256].once + (double)load * kCost[S_256x256].step : apart;
+    P.apart = plan_product(A0.M, A0.N, A0.steps, cus).us + plan_product(A1.M, A1.N, A1.steps, cus).us;
+    P.W.p[0] = A0;
+    P.W.p[1] = A1;
+    set_tiles(P.W.p[0], BM, BN, 1024);
+    set_tiles(P.W.p[1], BM, BN, 1024);
+    const int64_t load = pair_plan(P.W, cus);
+    P.large = load ? kCost[S_256x256].once + (double)load * kCost[S_256x256].step : P.apart;
 
     // two workgroups of 64 x 128 tiles per compute unit
     constexpr Cost c = kCost[S_R64x128];
-    RingPair Q;
-    Q.p[0] = A0;
-    Q.p[1] = A1;
-    set_tiles(Q.p[0], c.bm, c.bn, 1024);
-    set_tiles(Q.p[1], c.bm, c.bn, 1024);
-    Q.n0 = Q.p[0].cells;
-    Q.n1 = Q.p[1].cells;
-    Q.second_first = A1.steps > A0.steps;
-    double ring = apart;
-    if ((int64_t)Q.n0 + Q.n1 <= 2 * (int64_t)cus) {
+    P.Q.p[0] = A0;
+    P.Q.p[1] = A1;
+    set_tiles(P.Q.p[0], c.bm, c.bn, 1024);
+    set_tiles(P.Q.p[1], c.bm, c.bn, 1024);
+    P.Q.n0 = P.Q.p[0].cells;
+    P.Q.n1 = P.Q.p[1].cells;
+    P.Q.second_first = A1.steps > A0.steps;
+    P.small = P.apart;
+    if ((int64_t)P.Q.n0 + P.Q.n1 <= 2 * (int64_t)cus) {
         const double steps = std::max((double)std::max(A0.steps, A1.steps),
-                                      ((double)Q.n0 * A0.steps + (double)Q.n1 * A1.steps) / cus);
-        ring = c.once + c.round + 1.2 * steps * c.step; // two loads share the step
+                                      ((double)P.Q.n0 * A0.steps + (double)P.Q.n1 * A1.steps) / cus);
+        P.small = c.once + c.round + 1.2 * steps * c.step; // two loads share the step
     }
-    if (ring <= big && ring < 0.97 * apart) {
-        hipLaunchKernelGGL((mx_gemm_ring_pair_kernel<ELEM, R64x128>), dim3((unsigned)(Q.n0 + Q.n1)),
-                           dim3(R64x128::NT), 0, stream, Q);
+    P.mode = P.small <= P.large && P.small < 0.97 * P.apart ? PAIR_SMALL
+             : P.large < 0.97 * P.apart                     ? PAIR_LARGE
+                                                            : PAIR_APART;
+}
+
+// Products 0 (float output) and 1 (bf16 output) on one stream.
+template <int ELEM>
+hipError_t multiply_pair_as(const PairPlan &P, const Args &A0, const Args &A1, hipStream_t stream)
+{
+    if (P.mode == PAIR_SMALL) {
+        hipLaunchKernelGGL((mx_gemm_ring_pair_kernel<ELEM, R64x128>),
+                           dim3((unsigned)(P.Q.n0 + P.Q.n1)), dim3(R64x128::NT), 0, stream, P.Q);
         return hipGetLastError();
     }
-    if (big < 0.97 * apart) {
-        hipLaunchKernelGGL((mx_gemm_pair_kernel<ELEM>), dim3((unsigned)cus), dim3(NT), 0, stream, W);
+    if (P.mode == PAIR_LARGE) {
+        hipLaunchKernelGGL((mx_gemm_pair_kernel<ELEM>), dim3((unsigned)A0.grid_max), dim3(NT), 0,
+                           stream, P.W);
         return hipGetLastError();
     }
     const hipError_t e = multiply<ELEM, MX_OUT_BF16>(A1, stream);
     return e != hipSuccess ? e : multiply<ELEM, MX_OUT_F32>(A0, stream);
+}
+
+template <int ELEM> hipError_t multiply_pair(const Args &A0, const Args &A1, hipStream_t stream)
+{
+    PairPlan P;
+    plan_pair(P, A0, A1);
+    return multiply_pair_as<ELEM>(P, A0, A1, stream);
 }
 
 } // namespace mxg
@@ -786,3 +812,54 @@ mx_status matmul_pair(const Product &f32, const Product &bf16, int elem, hipStre
 }
 
 } // namespace mxg
+
+// ---------------------------------------------------- for the library's tests --
+
+namespace {
+
+// M, N and the K steps alone: what the plans depend on.
+bool plan_args(mxg::Args &A, int64_t M, int64_t N, int64_t K, int elem, int units)
+{
+    const int64_t rb = elem == MX_ELEM_E2M1 ? K / 2 : K;
+    if (M <= 0 || N <= 0 || K <= 0 || rb % mxg::KB != 0 || units <= 0)
+        return false;
+    A = mxg::Args{};
+    A.M = M;
+    A.N = N;
+    A.steps = (int)(rb / mxg::KB);
+    A.grid_max = units;
+    return true;
+}
+
+} // namespace
+
+extern "C" {
+
+int mxt_product_plan(int64_t M, int64_t N, int64_t K, int elem, int units, int *whole, int *tail,
+                     double *us)
+{
+    mxg::Args A;
+    if (!plan_args(A, M, N, K, elem, units))
+        return -1;
+    const mxg::Plan P = mxg::plan_product(M, N, A.steps, units);
+    *whole = P.whole;
+    *tail = P.tail;
+    *us = P.us;
+    return P.shape;
+}
+
+int mxt_pair_plan(int64_t M0, int64_t N0, int64_t K0, int64_t M1, int64_t N1, int64_t K1, int elem,
+                  int units, double *us)
+{
+    mxg::Args A0, A1;
+    if (!plan_args(A0, M0, N0, K0, elem, units) || !plan_args(A1, M1, N1, K1, elem, units))
+        return -1;
+    mxg::PairPlan P;
+    mxg::plan_pair(P, A0, A1);
+    us[0] = P.apart;
+    us[1] = P.large;
+    us[2] = P.small;
+    return P.mode;
+}
+
+} // extern "C"

@@ -13,4 +13,20 @@ extern "C" {
 // MXFP8 with blocks of 16, 32, 64, 3..5 MXFP4, 6 NVFP4; gain: a gamma is given.
 int mxt_norm_team(int64_t T, int64_t d, int kind, int fmt, int gain);
 
+// Tile shapes of mxt_product_plan: 0 .. 6 = 16 x 32, 32 x 32, 32 x 64 and 64 x
+// 64 with K split over the waves, 64 x 128 and 128 x 128 rings, 256 x 256.
+//
+// How mx_matmul_fwd computes [M, K] x [N, K]^T on `units` compute units:
+// returns the tile shape, or -1 for sizes it refuses; *whole > 0: that many
+// cells of 256 x 256 in a first launch and the rest in tiles of *tail in a
+// second.  *us: the estimate the choice was made by.
+int mxt_product_plan(int64_t M, int64_t N, int64_t K, int elem, int units, int *whole, int *tail,
+                     double *us);
+
+// How mxnorm_linear_bwd computes its two products (0: float output, 1: bf16):
+// 0 one after the other, 1 in one launch of 256 x 256 tiles, 2 in one launch
+// of 64 x 128 tiles; -1: refused.  us[3]: the three estimates.
+int mxt_pair_plan(int64_t M0, int64_t N0, int64_t K0, int64_t M1, int64_t N1, int64_t K1, int elem,
+                  int units, double *us);
+
 } // extern "C"

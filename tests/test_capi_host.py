@@ -9,6 +9,7 @@ import re
 import numpy as np
 import pytest
 
+import launch_rules
 from paper_2603_13180_amd import mxnorm
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -366,4 +367,16 @@ MX8_B32, MX4_B32, NV4 = 1, 4, 6                       # and its formats
 ])
 def test_norm_team_widths(T, d, kind, fmt, gain, lanes):
     # each width is the faster one measured at that size
-    assert mxnorm.load().mxt_norm_team(ctypes.c_int64(T), ctypes.c_int64(d), kind, fmt, gain) == lanes
+    assert launch_rules.norm_team(T, d, kind, fmt, gain) == lanes
+
+
+@pytest.mark.parametrize("T,N,d", [(1280, 17408, 5120), (19072, 4608, 7424), (1024, 2304, 768),
+                                   (4096, 6144, 4096), (4352, 6400, 4128), (32768, 6144, 4096)])
+def test_pair_estimates_count_the_plans_that_run(T, N, d):
+    # the backward weighs a shared launch against the two products as
+    # mx_matmul_fwd computes them: a second launch that saves less than 5%,
+    # which a product does not take, does not count (at the first two sizes
+    # it did, and kept the products apart)
+    _, us = launch_rules.pair_plan(T, N, d, "e4m3")
+    apart = sum(launch_rules.product_plan(*p, "e4m3")[3] for p in ((N, d, T), (T, d, N)))
+    assert us[0] == pytest.approx(apart, rel=1e-12)
