@@ -619,6 +619,7 @@ inline int64_t pair_plan(PairArgs &W, int cus)
 enum PairMode { PAIR_APART, PAIR_LARGE, PAIR_SMALL };
 struct PairPlan {
     int mode;
+    bool can_large;             // the shares of the large tiles were found
     double apart, large, small; // us; large or small = apart: not possible
     PairArgs W;
     RingPair Q;
@@ -633,6 +634,7 @@ inline void plan_pair(PairPlan &P, const Args &A0, const Args &A1)
     set_tiles(P.W.p[0], BM, BN, 1024);
     set_tiles(P.W.p[1], BM, BN, 1024);
     const int64_t load = pair_plan(P.W, cus);
+    P.can_large = load != 0;
     P.large = load ? kCost[S_256x256].once + (double)load * kCost[S_256x256].step : P.apart;
 
     // two workgroups of 64 x 128 tiles per compute unit
@@ -817,6 +819,15 @@ mx_status matmul_pair(const Product &f32, const Product &bf16, int elem, hipStre
 
 namespace {
 
+bool known_shape(int s) { return s >= 0 && s < mxg::S_COUNT; }
+
+template <int ELEM>
+hipError_t multiply_as(const mxg::Plan &P, const mxg::Args &A, int out_dtype, hipStream_t stream)
+{
+    return out_dtype == MX_OUT_F32 ? mxg::multiply_as<ELEM, MX_OUT_F32>(P, A, stream)
+                                   : mxg::multiply_as<ELEM, MX_OUT_BF16>(P, A, stream);
+}
+
 // M, N and the K steps alone: what the plans depend on.
 bool plan_args(mxg::Args &A, int64_t M, int64_t N, int64_t K, int elem, int units)
 {
@@ -860,6 +871,58 @@ int mxt_pair_plan(int64_t M0, int64_t N0, int64_t K0, int64_t M1, int64_t N1, in
     us[1] = P.large;
     us[2] = P.small;
     return P.mode;
+}
+
+mx_status mxt_matmul(const uint8_t *a_codes, const uint8_t *a_scales, const uint8_t *b_codes,
+                     const uint8_t *b_scales, int64_t M, int64_t N, int64_t K, int elem,
+                     const void *b_gain, int out_dtype, void *out, int shape, int whole, int units,
+                     hipStream_t stream)
+{
+    mxk::clear_error();
+    mxg::Args A;
+    const mx_status ok = matmul_args(A, a_codes, a_scales, b_codes, b_scales, M, N, K, 32, elem,
+                                     b_gain, out_dtype, out, stream);
+    if (ok != MX_OK || M == 0 || N == 0)
+        return ok;
+    const int64_t cells = ((M + mxg::BM - 1) / mxg::BM) * ((N + mxg::BN - 1) / mxg::BN);
+    if (!known_shape(shape) || whole < 0 || whole >= cells || units < 0 || units > A.grid_max)
+        return mxk::fail(MX_EINVAL, "no such tile shape, first launch or number of units");
+    if (units)
+        A.grid_max = units;
+    const mxg::Plan P{whole ? (int)mxg::S_256x256 : shape, whole, shape, 0.0};
+    const hipError_t e = elem == MX_ELEM_E4M3 ? multiply_as<MX_ELEM_E4M3>(P, A, out_dtype, stream)
+                                              : multiply_as<MX_ELEM_E2M1>(P, A, out_dtype, stream);
+    return e == hipSuccess ? MX_OK
+                           : mxk::fail(MX_EHIP, "kernel launch failed: %s", hipGetErrorString(e));
+}
+
+mx_status mxt_matmul_pair(const MxtProduct *f32, const MxtProduct *bf16, int elem, int mode,
+                          int units, hipStream_t stream)
+{
+    mxk::clear_error();
+    mxg::Args A0, A1;
+    mx_status ok = matmul_args(A0, f32->a, f32->as, f32->b, f32->bs, f32->M, f32->N, f32->K, 32,
+                               elem, f32->gain, MX_OUT_F32, f32->out, stream);
+    if (ok == MX_OK)
+        ok = matmul_args(A1, bf16->a, bf16->as, bf16->b, bf16->bs, bf16->M, bf16->N, bf16->K, 32,
+                         elem, bf16->gain, MX_OUT_BF16, bf16->out, stream);
+    if (ok != MX_OK)
+        return ok;
+    if (f32->M == 0 || f32->N == 0 || bf16->M == 0 || bf16->N == 0 || units < 0 ||
+        units > A0.grid_max)
+        return mxk::fail(MX_EINVAL, "empty product, or no such number of units");
+    if (units)
+        A0.grid_max = A1.grid_max = units;
+    mxg::PairPlan P;
+    mxg::plan_pair(P, A0, A1);
+    if (mode < 0 || mode > mxg::PAIR_SMALL || (mode == mxg::PAIR_LARGE && !P.can_large))
+        return mxk::fail(MX_EINVAL, "no such pair launch");
+    P.mode = mode;
+    const hipError_t e = elem == MX_ELEM_E4M3
+                             ? mxg::multiply_pair_as<MX_ELEM_E4M3>(P, A0, A1, stream)
+                             : mxg::multiply_pair_as<MX_ELEM_E2M1>(P, A0, A1, stream);
+    return e == hipSuccess ? MX_OK
+                           : mxk::fail(MX_EHIP, "kernel launch failed: %s", hipGetErrorString(e));
 }
 
 } // extern "C"

@@ -2,6 +2,8 @@
 entry points of libmxnorm.so)."""
 import ctypes
 
+import torch
+
 from paper_2603_13180_amd import mxnorm
 
 SHAPES = ["k16x32", "k32x32", "k32x64", "k64x64", "r64x128", "r128x128", "t256x256"]
@@ -9,7 +11,7 @@ PAIRS = ["apart", "large", "small"]
 ELEM = {"e4m3": 0, "e2m1": 1}
 UNITS = 256                                            # compute units of an MI355X
 
-_I, _L, _D = ctypes.c_int, ctypes.c_int64, ctypes.c_double
+_I, _L, _D, _P = ctypes.c_int, ctypes.c_int64, ctypes.c_double, ctypes.c_void_p
 
 
 def _fn(name, args):
@@ -44,3 +46,33 @@ def pair_plan(T, N, d, elem, units=UNITS):
                                                                   units, us)
     assert m >= 0, (T, N, d, elem)
     return PAIRS[m], list(us)
+
+
+def matmul_as(ac, as_, bc, bs, K, elem, shape, whole=0, units=0, out=None, b_gain=None,
+              out_dtype=torch.float32):
+    """mx_matmul_fwd in tiles of `shape` (or `whole` cells of 256 x 256 first),
+    the persistent kernels as on `units` compute units; GPU tensors."""
+    M, N = ac.shape[0], bc.shape[0]
+    if out is None:
+        out = torch.empty(M, N, dtype=out_dtype, device=ac.device)
+    f = _fn("mxt_matmul", [_P] * 4 + [_L] * 3 + [_I, _P, _I, _P, _I, _I, _I, _P])
+    mxnorm._check(f(ac.data_ptr(), as_.data_ptr(), bc.data_ptr(), bs.data_ptr(), M, N, K, ELEM[elem],
+                    None if b_gain is None else b_gain.data_ptr(), mxnorm.OUT_DTYPES[out.dtype],
+                    out.data_ptr(), SHAPES.index(shape), whole, units, mxnorm._stream(ac.device)))
+    return out
+
+
+class _Product(ctypes.Structure):
+    _fields_ = [(n, _P) for n in ("a", "as_", "b", "bs")] + [(n, _L) for n in "MNK"] + \
+        [("gain", _P), ("out", _P)]
+
+
+def matmul_pair_as(f32, bf16, elem, mode, units=0):
+    """Two products at once; each (a codes, a scales, b codes, b scales, K,
+    gain or None, out)."""
+    def product(a, as_, b, bs, K, gain, out):
+        return _Product(a.data_ptr(), as_.data_ptr(), b.data_ptr(), bs.data_ptr(), a.shape[0],
+                        b.shape[0], K, None if gain is None else gain.data_ptr(), out.data_ptr())
+    f = _fn("mxt_matmul_pair", [_P, _P, _I, _I, _I, _P])
+    mxnorm._check(f(ctypes.byref(product(*f32)), ctypes.byref(product(*bf16)), ELEM[elem],
+                    PAIRS.index(mode), units, mxnorm._stream(f32[0].device)))

@@ -6,8 +6,9 @@ The matrix cores multiply E4M3/E2M1 elements exactly and apply each
 own internal alignment: terms far below the largest product of one
 instruction can be dropped.  The test bound is |H - H_oracle| <=
 2^-9 * sum_k |A[m][k] B[n][k]| (plus half a bf16 ulp of H for bf16 output);
-the exactness test below (at most one product per output) pins the operand
-layout and the scale association bit for bit.
+the exactness tests (at most one product per output) pin the operand layout
+and the scale association bit for bit: below for the kernel chosen at that
+size, in test_gpu_tile_shapes.py for every kernel.
 """
 import os
 from concurrent.futures import ThreadPoolExecutor
@@ -16,6 +17,7 @@ import numpy as np
 import pytest
 import torch
 
+import launch_rules
 import oracle
 from paper_2603_13180_amd import mxnorm, synth
 
@@ -186,12 +188,12 @@ def test_mxnorm_linear_forward(block_elem, T, d, N):
 
 # ------------------------------------------- the benchmarked shapes --
 #
-# The kernel maps workgroups to 256 x 256 output tiles through an XCD-aware
-# renumbering and visits tile rows in groups of 4.  These tests run it at the
-# Llama-3-8B projection shapes the layer benchmark times (d = 4096; QKV N =
-# 6144, gate+up N = 28672) and at a mid-size shape compared in full, so that
-# several complete groups, the ragged last group and the full K = 4096 loop
-# are checked against the oracle.
+# At these sizes the kernel maps workgroups to 256 x 256 output tiles through an
+# XCD-aware renumbering and visits tile rows in groups of 4.  These tests run it
+# at the Llama-3-8B projection shapes the layer benchmark times (d = 4096; QKV N
+# = 6144, gate+up N = 28672), and the 128 x 128 tiles at a mid-size shape
+# compared in full, so that several complete groups, the ragged last group and
+# the full K = 4096 loop are checked against the oracle.
 
 WORKERS = max(1, min(16, os.cpu_count() or 1))
 
@@ -279,8 +281,9 @@ def test_gate_up_shape_sampled(elem, out_dtype):
 
 @pytest.mark.parametrize("elem", ELEMS)
 def test_mid_shape_every_output(elem):
-    # 9 tile rows (two full groups of 4 and a group of 1) x 5 tile columns
-    # (the last one 16 columns wide), K = 4096: every output compared
+    # 18 x 9 tiles of 128 x 128, the last column of them 16 wide, K = 4096:
+    # every output compared (the 256 x 256 tiles of this size are in
+    # test_gpu_tile_shapes.py)
     M, N, K = 2304, 1040, 4096
     rng = np.random.default_rng(51 + len(elem))
     ac, as_ = random_operand(M, K, elem, rng)
@@ -293,24 +296,44 @@ def test_mid_shape_every_output(elem):
                      "mid %s %s every output" % (elem, out_dtype))
 
 
-# one size or more for every tile shape the product chooses from, at the edges
-# of its tiles: rows and columns one past and one short of a tile, fewer K
-# steps than waves share out, and a step count no wave count divides
+# one size or more for every plan mx_matmul_fwd chooses from (the expected one
+# is checked, so that a change of the rule shows here), at the edges of its
+# tiles: rows and columns one past and one short of a tile, fewer K steps than
+# waves share out, a step count no wave count divides, and whole rounds of 256
+# x 256 cells followed by ragged cells in each smaller shape
+PLANS = [
+    ("k16x32", (1, 16, 256)), ("k16x32", (16, 496, 1280)), ("k16x32", (17, 528, 2816)),
+    ("k16x32", (16, 6144, 4096)), ("k16x32", (31, 2064, 2304)),
+    ("k32x32", (257, 528, 2048)), ("k32x32", (17, 7472, 1024)), ("k32x32", (49, 3536, 512)),
+    ("k32x64", (65, 4112, 768)), ("k32x64", (47, 6032, 1536)),
+    ("k64x64", (33, 10256, 1280)), ("k64x64", (127, 6160, 2304)), ("k64x64", (1000, 784, 2304)),
+    ("r64x128", (61, 20496, 768)), ("r64x128", (257, 6128, 1280)), ("r64x128", (277, 5936, 2048)),
+    ("r128x128", (2305, 784, 1024)), ("r128x128", (1537, 2064, 3328)),
+    ("t256x256", (1000, 8208, 512)), ("t256x256", (1962, 5808, 2048)),
+    ("t256x256+k16x32", (4624, 6672, 2048)), ("t256x256+k32x32", (6437, 2320, 2048)),
+    ("t256x256+k32x64", (8217, 1808, 2048)), ("t256x256+k64x64", (4676, 3360, 2048)),
+    ("t256x256+r64x128", (6201, 2576, 2048)), ("t256x256+r128x128", (4127, 4128, 2048)),
+]
+
+
+def test_plans_are_the_expected_ones():
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    for plan, (M, N, K) in PLANS:
+        for elem in ELEMS:
+            assert launch_rules.shape_of(M, N, K, elem, units=units) == plan, (M, N, K, elem)
+
+
 @pytest.mark.parametrize("elem", ELEMS)
-@pytest.mark.parametrize("M,N,K", [
-    (1, 16, 256), (16, 496, 1280), (17, 528, 2816),        # 16 x 32 and 32 x 32 tiles, K split
-    (16, 6144, 4096), (31, 2064, 2304),
-    (33, 10256, 1280), (65, 4112, 768),                    # 32 x 64
-    (127, 6160, 2304), (1000, 784, 2304),                  # 64 x 64
-    (61, 20496, 768), (257, 6128, 1280), (2305, 784, 1024),  # ring, 64 x 128
-    (1000, 8208, 512), (1537, 2064, 3328),                 # ring, 128 x 128
-])
-def test_tile_shapes_every_output(elem, M, N, K):
+@pytest.mark.parametrize("plan,size", PLANS)
+def test_tile_shapes_every_output(elem, plan, size):
+    M, N, K = size
     rng = np.random.default_rng(M + 3 * N + 5 * K + len(elem))
     ac, as_ = random_operand(M, K, elem, rng)
     bc, bs = random_operand(N, K, elem, rng)
     gain = torch.from_numpy(rng.standard_normal(N).astype(np.float32)).to(torch.bfloat16)
     rows = tile_sample(M, tile=16, lead=2, tail=2, extra=4, seed=M)
+    if "+" in plan:   # and rows of the second launch's cells, the last ones
+        rows = np.unique(np.r_[rows, M - 300:M:37])
     want, mag = oracle_product(ac[rows], as_[rows], bc, bs, K, elem)
     t = [dev_u8(v) for v in (ac, as_, bc, bs)]
     gf = gain.double().numpy()
