@@ -464,21 +464,40 @@ using K64x64 = KSplit<64, 64, 8, 1>;
 enum Shape { S_K16x32, S_K32x32, S_K32x64, S_K64x64, S_R64x128, S_R128x128, S_256x256, S_COUNT };
 
 // What a launch of each tile shape costs on MI355X, fitted to times at K =
-// 512 .. 8192 and 64 to 3400 tiles (E4M3; E2M1 moves the same bytes per step
-// and is within 15%): us once per launch, per round of tiles (their stores,
-// and for the K-split kernel the start of a tile's loads, which nothing
-// overlaps) and per K step of a round.  Below 256 x 256 the time per step is
-// the tile's operand bytes at about 55 GB/s per compute unit, so a larger
-// tile does more products per byte and a smaller one leaves fewer compute
-// units idle.
+// 512 .. 8192 and 64 to 3400 tiles: us once per launch, per round of tiles
+// (their stores, and for the K-split kernel the start of a tile's loads, which
+// nothing overlaps) and per K step of a round.  Below 256 x 256 the time per
+// step is the tile's operand bytes at about 55 GB/s per compute unit, so a
+// larger tile does more products per byte and a smaller one leaves fewer
+// compute units idle.
+//
+// With few K steps a smaller tile's latency is not covered (a ring waits for
+// the stores of the tile before, a K-split tile for its only step): many
+// rounds take `few` + steps * `few_step` each at least.  At one K step, bf16,
+// 128 x 128 tiles then take 2.3-2.5 us a round, not 1.4, and lose to 256 x
+// 256: 9526 x 22336 129 against 106 us, 142102 x 1152 97 against 70.  Counted
+// from the ninth round on for the rings (with fewer rounds 256 x 256 tiles do
+// not reach their pace either: two K steps, 3 to 8 rounds, the rings are 1.05
+// to 1.1 times as fast in the median), from the first if N leaves half of the
+// 64 x 128 tile empty (63697 x 48 10.5 against 8.0), and for the K-split tiles
+// beyond two rounds.  Over 1000 sizes of 1 to 4 steps and 1e6 to 2e8 outputs
+// the choice was more than 3% slower than 256 x 256 tiles at 106, by up to 28%,
+// and is now at 35, 32 of them of one step, by up to 16%; on average it is
+// 1.15 times as fast as those.
+//
+// An estimate ranks the shapes; it does not predict the time.  It has no term
+// for operands that come from HBM rather than L2, nor for the output's type:
+// 61 x 28672 x 4096 is put at 17 us in E4M3 and takes 34, and at 10 in E2M1
+// and takes 14.
 struct Cost {
     int bm, bn;
-    float once, round, step;
+    float once, round, step, few, few_step;
 };
 constexpr Cost kCost[S_COUNT] = {
-    {16, 32, 1.3f, 1.0f, 0.14f},  {32, 32, 1.4f, 1.1f, 0.14f},  {32, 64, 2.2f, 0.7f, 0.19f},
-    {64, 64, 0.4f, 2.6f, 0.275f}, {64, 128, 3.1f, 0.4f, 0.425f}, {128, 128, 4.1f, 0.8f, 0.59f},
-    {256, 256, 1.2f, 4.0f, 1.75f},
+    {16, 32, 1.3f, 1.0f, 0.14f, 1.6f, 0.0f},   {32, 32, 1.4f, 1.1f, 0.14f, 1.9f, 0.0f},
+    {32, 64, 2.2f, 0.7f, 0.19f, 2.15f, 0.0f},  {64, 64, 0.4f, 2.6f, 0.275f, 2.9f, 0.2f},
+    {64, 128, 3.1f, 0.4f, 0.425f, 1.1f, 0.3f}, {128, 128, 4.1f, 0.8f, 0.59f, 1.8f, 0.45f},
+    {256, 256, 1.2f, 4.0f, 1.75f, 0.0f, 0.0f},
 };
 
 // us a launch over `cells` outputs of cm x cn takes on `cus` compute units
@@ -487,7 +506,14 @@ inline double launch_cost(int shape, int64_t cells, int64_t cm, int64_t cn, int 
     const Cost &c = kCost[shape];
     const int64_t tiles = cells * ((cm + c.bm - 1) / c.bm) * ((cn + c.bn - 1) / c.bn);
     const int64_t rounds = (tiles + cus - 1) / cus;
-    return c.once + (double)rounds * (c.round + (double)steps * c.step);
+    const double per = c.round + (double)steps * c.step;
+    const double few = std::max(per, (double)c.few + (double)steps * c.few_step);
+    if (shape <= S_K64x64)
+        return c.once + (double)rounds * (rounds > 2 ? few : per);
+    double us = (double)rounds * per + (double)std::max<int64_t>(0, rounds - 8) * (few - per);
+    if (shape == S_R64x128 && cn <= 64 && rounds > 2)
+        us = std::max(us, (double)rounds * (1.3 + 0.3 * (double)steps));
+    return c.once + us;
 }
 
 // How one product is computed: the whole output in tiles of `shape`; or, where

@@ -380,3 +380,17 @@ def test_pair_estimates_count_the_plans_that_run(T, N, d):
     _, us = launch_rules.pair_plan(T, N, d, "e4m3")
     apart = sum(launch_rules.product_plan(*p, "e4m3")[3] for p in ((N, d, T), (T, d, N)))
     assert us[0] == pytest.approx(apart, rel=1e-12)
+
+
+@pytest.mark.parametrize("M,N,K,elem,shape", [
+    # few K steps, many tiles: a small tile's latency is not covered
+    (9526, 22336, 256, "e2m1", "t256x256"), (14783, 18560, 256, "e2m1", "t256x256"),
+    (19013, 2880, 128, "e4m3", "t256x256"), (142102, 1152, 128, "e4m3", "t256x256"),
+    (100469, 1376, 384, "e4m3", "t256x256"), (204865, 64, 128, "e4m3", "r128x128"),
+    # few steps where smaller tiles win all the same, and more steps
+    (2255, 1520, 128, "e4m3", "r64x128"), (11290, 1616, 256, "e4m3", "r128x128"),
+    (1000, 8192, 2048, "e4m3", "r128x128"), (16, 6144, 4096, "e4m3", "k16x32"),
+    (61, 28672, 4096, "e2m1", "r64x128"), (8192, 6144, 4096, "e4m3", "t256x256"),
+])
+def test_product_plan_at_few_k_steps(M, N, K, elem, shape):
+    assert launch_rules.shape_of(M, N, K, elem) == shape
