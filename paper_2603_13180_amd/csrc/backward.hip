@@ -375,13 +375,13 @@ __device__ __forceinline__ void cast_rows(const CastTArgs &A, uint8_t *codes, ui
 // The backward's four casts in one launch: grad_H by rows and by columns from
 // one read of it, W and rho X by columns.  HBM bound at large sizes: 32768 x
 // 6144 x 4096 (E4M3) 298 us as four launches, 218 us here (5.9 TB/s); launch
-// and latency bound at small ones: 1024 x 2304 x 768 23 -> 9 us.  Workgroups start[j] .. start[j + 1]
-// - 1 take job j's tiles (starts are multiples of 8, so that a tile's number
+// and latency bound at small ones: 1024 x 2304 x 768 23 -> 9 us.  Workgroups from start[j] on
+// take job j's tiles (starts are multiples of 8, so that a tile's number
 // keeps its XCD).
 struct CastJobs {
     CastTArgs job[3];
     uint8_t *row_codes, *row_scales; // job 0's row cast
-    int start[4];
+    int start[3];
 };
 
 template <bool FP4, int COLS, int NTH>
@@ -833,12 +833,11 @@ mx_status scratch_for(hipStream_t stream, void **out)
 
 } // namespace
 
-extern "C" {
+namespace mxb {
 
-mx_status mx_cast_t_fwd(const void *x, const float *rho, int64_t R, int64_t C, int block,
-                        int elem, int scale_mode, uint8_t *codes, uint8_t *scales, hipStream_t stream)
+mx_status check_cast_t(const void *x, const float *rho, int64_t R, int64_t C, int block, int elem,
+                       int scale_mode, const uint8_t *codes, const uint8_t *scales)
 {
-    mxk::clear_error();
     if (R < 0 || C <= 0)
         return mxk::fail(MX_EINVAL, "R must be >= 0 and C > 0");
     if (elem != MX_ELEM_E4M3 && elem != MX_ELEM_E2M1)
@@ -859,6 +858,54 @@ mx_status mx_cast_t_fwd(const void *x, const float *rho, int64_t R, int64_t C, i
         return mxk::fail(MX_EINVAL, "x, codes and scales must be non-NULL");
     if (!aligned(x, 16) || !aligned(codes, 16) || (rho && !aligned(rho, 4)))
         return mxk::fail(MX_EINVAL, "x and codes must be 16-byte, rho 4-byte aligned");
+    return MX_OK;
+}
+
+mx_status check_ste(const void *x, const void *grad_z, const void *gamma, const float *rho,
+                    int64_t T, int64_t d, int out_dtype, const void *grad_x, const float *grad_gamma,
+                    const void *workspace, size_t workspace_bytes)
+{
+    if (T < 0)
+        return mxk::fail(MX_EINVAL, "T must be >= 0");
+    if (d <= 0 || d % 8 != 0)
+        return mxk::fail(MX_EINVAL, "d must be a positive multiple of 8");
+    if (d > MXNORM_MAX_D)
+        return mxk::fail(MX_EUNSUPPORTED, "d = %lld exceeds %d", (long long)d, MXNORM_MAX_D);
+    if (out_dtype != MX_OUT_F32 && out_dtype != MX_OUT_BF16)
+        return mxk::fail(MX_EINVAL, "out_dtype must be MX_OUT_F32 or MX_OUT_BF16");
+    if (T == 0)
+        return MX_OK;
+    if (!x || !grad_z || !rho || !grad_x)
+        return mxk::fail(MX_EINVAL, "x, grad_z, rho and grad_x must be non-NULL");
+    if (!aligned(x, 16) || !aligned(grad_z, 16) || (gamma && !aligned(gamma, 16)) ||
+        !aligned(grad_x, 16) || !aligned(rho, 4))
+        return mxk::fail(MX_EINVAL, "x, grad_z, gamma and grad_x must be 16-byte, rho 4-byte "
+                                    "aligned");
+    if (grad_gamma) {
+        if (!aligned(grad_gamma, 4))
+            return mxk::fail(MX_EINVAL, "grad_gamma must be 4-byte aligned");
+        if (!workspace || !aligned(workspace, 16) ||
+            workspace_bytes < mxnorm_ste_bwd_workspace_bytes(T, d))
+            return mxk::fail(MX_EINVAL, "grad_gamma needs a 16-byte aligned workspace of "
+                                        "mxnorm_ste_bwd_workspace_bytes(T, d) = %zu bytes",
+                             mxnorm_ste_bwd_workspace_bytes(T, d));
+    }
+    if (ste_workgroups(T) > INT32_MAX)
+        return mxk::fail(MX_EUNSUPPORTED, "T too large");
+    return MX_OK;
+}
+
+} // namespace mxb
+
+extern "C" {
+
+mx_status mx_cast_t_fwd(const void *x, const float *rho, int64_t R, int64_t C, int block,
+                        int elem, int scale_mode, uint8_t *codes, uint8_t *scales, hipStream_t stream)
+{
+    mxk::clear_error();
+    const mx_status ok = mxb::check_cast_t(x, rho, R, C, block, elem, scale_mode, codes, scales);
+    if (ok != MX_OK || R == 0)
+        return ok;
     mxb::CastTArgs A;
     A.x = static_cast<const uint16_t *>(x);
     A.rho = rho;
@@ -901,33 +948,10 @@ mx_status mxnorm_ste_bwd(const void *x, const void *grad_z, const void *gamma, c
                          void *workspace, size_t workspace_bytes, hipStream_t stream)
 {
     mxk::clear_error();
-    if (T < 0)
-        return mxk::fail(MX_EINVAL, "T must be >= 0");
-    if (d <= 0 || d % 8 != 0)
-        return mxk::fail(MX_EINVAL, "d must be a positive multiple of 8");
-    if (d > MXNORM_MAX_D)
-        return mxk::fail(MX_EUNSUPPORTED, "d = %lld exceeds %d", (long long)d, MXNORM_MAX_D);
-    if (out_dtype != MX_OUT_F32 && out_dtype != MX_OUT_BF16)
-        return mxk::fail(MX_EINVAL, "out_dtype must be MX_OUT_F32 or MX_OUT_BF16");
-    if (T == 0)
-        return MX_OK;
-    if (!x || !grad_z || !rho || !grad_x)
-        return mxk::fail(MX_EINVAL, "x, grad_z, rho and grad_x must be non-NULL");
-    if (!aligned(x, 16) || !aligned(grad_z, 16) || (gamma && !aligned(gamma, 16)) ||
-        !aligned(grad_x, 16) || !aligned(rho, 4))
-        return mxk::fail(MX_EINVAL, "x, grad_z, gamma and grad_x must be 16-byte, rho 4-byte "
-                                    "aligned");
-    if (grad_gamma) {
-        if (!aligned(grad_gamma, 4))
-            return mxk::fail(MX_EINVAL, "grad_gamma must be 4-byte aligned");
-        if (!workspace || !aligned(workspace, 16) ||
-            workspace_bytes < mxnorm_ste_bwd_workspace_bytes(T, d))
-            return mxk::fail(MX_EINVAL, "grad_gamma needs a 16-byte aligned workspace of "
-                                        "mxnorm_ste_bwd_workspace_bytes(T, d) = %zu bytes",
-                             mxnorm_ste_bwd_workspace_bytes(T, d));
-    }
-    if (ste_workgroups(T) > INT32_MAX)
-        return mxk::fail(MX_EUNSUPPORTED, "T too large");
+    const mx_status ok = mxb::check_ste(x, grad_z, gamma, rho, T, d, out_dtype, grad_x, grad_gamma,
+                                        workspace, workspace_bytes);
+    if (ok != MX_OK || T == 0)
+        return ok;
     mxb::SteArgs A;
     A.x = static_cast<const uint16_t *>(x);
     A.gz = static_cast<const uint16_t *>(grad_z);
@@ -1016,10 +1040,10 @@ mx_status backward_casts(const void *grad_h, const void *x, const float *rho, co
         J.start[j] = (int)at;
         const int64_t tiles = ((J.job[j].C + kCols - 1) / kCols) * ((J.job[j].R + CT_ROWS - 1) / CT_ROWS);
         at += (tiles + 7) / 8 * 8;
-        if (at > INT32_MAX)
+        // (no matrices that fit 288 GB of memory come near this)
+        if (at > (int64_t)(UINT32_MAX / kThreads))
             return mxk::fail(MX_EUNSUPPORTED, "too many tiles to cast in one launch");
     }
-    J.start[3] = (int)at;
     if (elem == MX_ELEM_E4M3)
         hipLaunchKernelGGL((cast_jobs_kernel<false, kCols, kThreads>), dim3((unsigned)at),
                            dim3(kThreads), 0, stream, J);

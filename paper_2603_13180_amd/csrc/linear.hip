@@ -99,9 +99,14 @@ mx_status mxnorm_linear_fwd(const void *x, int64_t T, int64_t d, const uint8_t *
     if (st != MX_OK)
         return st;
     const FwdSpace s(workspace, T, d, block > 0 ? block : 1, elem);
-    st = mxnorm_mx_fwd(x, T, d, block, elem, p, coef, eps, scale_mode, s.codes, s.scales, rho,
-                       stream);
-    if (st != MX_OK)
+    // both parts' checks come before the first launch
+    float c = coef;
+    if ((st = mxk::check_mxnorm(x, T, d, block, elem, p, c, eps, scale_mode, s.codes, s.scales,
+                                rho)) != MX_OK ||
+        (st = mxg::check_product({s.codes, s.scales, w_codes, w_scales, T, N, d, nullptr, out},
+                                 block, elem, out_dtype)) != MX_OK ||
+        (st = mxnorm_mx_fwd(x, T, d, block, elem, p, coef, eps, scale_mode, s.codes, s.scales, rho,
+                            stream)) != MX_OK)
         return st;
     return mx_matmul_fwd(s.codes, s.scales, w_codes, w_scales, T, N, d, block, elem, nullptr,
                          out_dtype, out, stream);
@@ -127,43 +132,29 @@ mx_status mxnorm_linear_bwd(const void *grad_h, const void *x, const float *rho,
         return st;
     const BwdSpace s(workspace, T, N, d, elem);
     const int mode = MX_SCALE_RCEIL;
-    // One launch for the casts and one, where it pays, for both products, if
-    // every part of the backward takes these arguments; else part by part,
-    // which reports what is wrong with them.
-    const int64_t kstep = elem == MX_ELEM_E2M1 ? 256 : 128;
-    auto at16 = [](const void *p) { return p && ((uintptr_t)p & 15) == 0; };
-    if (T > 0 && N > 0 && d > 0 && block == 32 && known(elem) && T % kstep == 0 && N % kstep == 0 &&
-        d % 32 == 0 && d <= MXNORM_MAX_D && T <= MX_MATMUL_MAX_K && N <= MX_MATMUL_MAX_K &&
-        N <= MXNORM_MAX_D && (out_dtype == MX_OUT_F32 || out_dtype == MX_OUT_BF16) && at16(grad_h) &&
-        at16(x) && at16(w) && at16(grad_x) && at16(grad_w) && (!gamma || at16(gamma)) && rho &&
-        ((uintptr_t)rho & 3) == 0) {
-        if ((st = mxb::backward_casts(grad_h, x, rho, w, T, N, d, elem,
-                                      {s.gh, s.gh_s, s.ght, s.ght_s, s.wt, s.wt_s, s.xt, s.xt_s},
-                                      stream)) != MX_OK ||
-            (st = mxg::matmul_pair({s.ght, s.ght_s, s.xt, s.xt_s, N, d, T, gamma, grad_w},
-                                   {s.gh, s.gh_s, s.wt, s.wt_s, T, d, N, nullptr, s.gz}, elem,
-                                   stream)) != MX_OK)
-            return st;
-        return mxnorm_ste_bwd(x, s.gz, gamma, rho, T, d, out_dtype, grad_x, grad_gamma, s.ste,
-                              s.ste_bytes, stream);
-    }
-    // grad_Z = MXCast(grad_H) MXCast_N(W), both blocked along N
-    if ((st = mx_cast_fwd(grad_h, nullptr, T, N, block, elem, mode, s.gh, s.gh_s, stream)) != MX_OK ||
-        (st = mx_cast_t_fwd(w, nullptr, N, d, block, elem, mode, s.wt, s.wt_s, stream)) != MX_OK)
+    const mxg::Product gz{s.gh, s.gh_s, s.wt, s.wt_s, T, d, N, nullptr, s.gz};
+    const mxg::Product gw{s.ght, s.ght_s, s.xt, s.xt_s, N, d, T, gamma, grad_w};
+    // the parts' checks, in the parts' order, before the first launch
+    if ((st = mxk::check_cast(grad_h, nullptr, T, N, block, elem, mode, s.gh, s.gh_s)) != MX_OK ||
+        (st = mxb::check_cast_t(w, nullptr, N, d, block, elem, mode, s.wt, s.wt_s)) != MX_OK ||
+        (st = mxg::check_product(gz, block, elem, MX_OUT_BF16)) != MX_OK ||
+        (st = mxb::check_ste(x, s.gz, gamma, rho, T, d, out_dtype, grad_x, grad_gamma, s.ste,
+                             s.ste_bytes)) != MX_OK ||
+        (st = mxb::check_cast_t(grad_h, nullptr, T, N, block, elem, mode, s.ght, s.ght_s)) != MX_OK ||
+        (st = mxb::check_cast_t(x, rho, T, d, block, elem, mode, s.xt, s.xt_s)) != MX_OK ||
+        (st = mxg::check_product(gw, block, elem, MX_OUT_F32)) != MX_OK)
         return st;
-    if ((st = mx_matmul_fwd(s.gh, s.gh_s, s.wt, s.wt_s, T, d, N, block, elem, nullptr, MX_OUT_BF16,
-                            s.gz, stream)) != MX_OK)
+    // (T, N and d are positive here: a product's K, a cast's columns)
+    // grad_Z = MXCast(grad_H) MXCast_N(W), both blocked along N; grad_W =
+    // (MXCast(grad_H^T) MXCast(rho~ X)^T) . gamma, blocked along T; then
+    // grad_X and grad_gamma
+    if ((st = mxb::backward_casts(grad_h, x, rho, w, T, N, d, elem,
+                                  {s.gh, s.gh_s, s.ght, s.ght_s, s.wt, s.wt_s, s.xt, s.xt_s},
+                                  stream)) != MX_OK ||
+        (st = mxg::matmul_pair(gw, gz, elem, stream)) != MX_OK)
         return st;
-    // grad_X, grad_gamma
-    if ((st = mxnorm_ste_bwd(x, s.gz, gamma, rho, T, d, out_dtype, grad_x, grad_gamma, s.ste,
-                             s.ste_bytes, stream)) != MX_OK)
-        return st;
-    // grad_W = (MXCast(grad_H^T) MXCast(rho~ X)^T) . gamma, blocked along T
-    if ((st = mx_cast_t_fwd(grad_h, nullptr, T, N, block, elem, mode, s.ght, s.ght_s, stream)) != MX_OK ||
-        (st = mx_cast_t_fwd(x, rho, T, d, block, elem, mode, s.xt, s.xt_s, stream)) != MX_OK)
-        return st;
-    return mx_matmul_fwd(s.ght, s.ght_s, s.xt, s.xt_s, N, d, T, block, elem, gamma, MX_OUT_F32,
-                         grad_w, stream);
+    return mxnorm_ste_bwd(x, s.gz, gamma, rho, T, d, out_dtype, grad_x, grad_gamma, s.ste,
+                          s.ste_bytes, stream);
 }
 
 } // extern "C"

@@ -742,14 +742,13 @@ int compute_units(hipStream_t stream)
     return n;
 }
 
-// The product's arguments, checked (see mx_matmul_fwd in the header); MX_OK
-// with M or N zero leaves `A` unset.
-mx_status matmul_args(mxg::Args &A, const uint8_t *a_codes, const uint8_t *a_scales,
-                      const uint8_t *b_codes, const uint8_t *b_scales, int64_t M, int64_t N,
-                      int64_t K, int block, int elem, const void *b_gain, int out_dtype, void *out,
-                      hipStream_t stream)
+} // namespace
+
+namespace mxg {
+
+mx_status check_product(const Product &P, int block, int elem, int out_dtype)
 {
-    if (M < 0 || N < 0 || K <= 0)
+    if (P.M < 0 || P.N < 0 || P.K <= 0)
         return mxk::fail(MX_EINVAL, "M and N must be >= 0 and K > 0");
     if (elem != MX_ELEM_E4M3 && elem != MX_ELEM_E2M1)
         return mxk::fail(MX_EINVAL, "elem must be MX_ELEM_E4M3 or MX_ELEM_E2M1");
@@ -758,38 +757,46 @@ mx_status matmul_args(mxg::Args &A, const uint8_t *a_codes, const uint8_t *a_sca
     if (block != 32)
         return mxk::fail(MX_EUNSUPPORTED, "the matrix cores apply one scale per 32 elements: block must be 32");
     const int64_t kstep = elem == MX_ELEM_E2M1 ? 256 : 128;
-    if (K % kstep != 0)
+    if (P.K % kstep != 0)
         return mxk::fail(MX_EUNSUPPORTED, "K must be a multiple of 128 (E4M3) or 256 (E2M1)");
-    if (N % 16 != 0)
+    if (P.N % 16 != 0)
         return mxk::fail(MX_EUNSUPPORTED, "N must be a multiple of 16");
-    if (K > MX_MATMUL_MAX_K)
+    if (P.K > MX_MATMUL_MAX_K)
         return mxk::fail(MX_EUNSUPPORTED, "K exceeds %d", MX_MATMUL_MAX_K);
-    if (M == 0 || N == 0)
+    if (P.M == 0 || P.N == 0)
         return MX_OK;
-    if (!a_codes || !a_scales || !b_codes || !b_scales || !out)
+    if (!P.a || !P.as || !P.b || !P.bs || !P.out)
         return mxk::fail(MX_EINVAL, "NULL pointer");
-    if (!aligned(a_codes, 16) || !aligned(b_codes, 16) || !aligned(a_scales, 4) ||
-        !aligned(b_scales, 4) || !aligned(out, 16) ||
-        (b_gain && !aligned(b_gain, 8)))
+    if (!aligned(P.a, 16) || !aligned(P.b, 16) || !aligned(P.as, 4) || !aligned(P.bs, 4) ||
+        !aligned(P.out, 16) || (P.gain && !aligned(P.gain, 8)))
         return mxk::fail(MX_EINVAL, "codes and out must be 16-byte, scales 4-byte and b_gain "
                                "8-byte aligned");
-    const int64_t tm = (M + mxg::BM - 1) / mxg::BM, tn = (N + mxg::BN - 1) / mxg::BN;
-    if (tm * tn > INT32_MAX / 2 || M > INT32_MAX || N > MX_MATMUL_MAX_N)
+    const int64_t tm = (P.M + BM - 1) / BM, tn = (P.N + BN - 1) / BN;
+    if (tm * tn > INT32_MAX / 2 || P.M > INT32_MAX || P.N > MX_MATMUL_MAX_N)
         return mxk::fail(MX_EUNSUPPORTED, "problem too large (N at most %d)", MX_MATMUL_MAX_N);
-    A.a = a_codes;
-    A.as = a_scales;
-    A.b = b_codes;
-    A.bs = b_scales;
-    A.bgain = static_cast<const uint16_t *>(b_gain);
-    A.out = out;
-    A.M = M;
-    A.N = N;
-    A.rb = elem == MX_ELEM_E2M1 ? K / 2 : K;
-    A.rs = K / 32;
+    return MX_OK;
+}
+
+} // namespace mxg
+
+namespace {
+
+// A checked product's kernel arguments.
+void product_args(mxg::Args &A, const mxg::Product &P, int elem, hipStream_t stream)
+{
+    A.a = P.a;
+    A.as = P.as;
+    A.b = P.b;
+    A.bs = P.bs;
+    A.bgain = static_cast<const uint16_t *>(P.gain);
+    A.out = P.out;
+    A.M = P.M;
+    A.N = P.N;
+    A.rb = elem == MX_ELEM_E2M1 ? P.K / 2 : P.K;
+    A.rs = P.K / 32;
     A.steps = (int)(A.rb / mxg::KB);
     const int cus = compute_units(stream);
     A.grid_max = cus > 0 ? cus : 256;
-    return MX_OK;
 }
 
 } // namespace
@@ -801,11 +808,12 @@ mx_status mx_matmul_fwd(const uint8_t *a_codes, const uint8_t *a_scales, const u
                         int elem, const void *b_gain, int out_dtype, void *out, hipStream_t stream)
 {
     mxk::clear_error();
-    mxg::Args A;
-    const mx_status ok = matmul_args(A, a_codes, a_scales, b_codes, b_scales, M, N, K, block, elem,
-                                     b_gain, out_dtype, out, stream);
+    const mxg::Product P{a_codes, a_scales, b_codes, b_scales, M, N, K, b_gain, out};
+    const mx_status ok = mxg::check_product(P, block, elem, out_dtype);
     if (ok != MX_OK || M == 0 || N == 0)
         return ok;
+    mxg::Args A;
+    product_args(A, P, elem, stream);
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipError_t e;
     if (elem == MX_ELEM_E4M3)
@@ -826,13 +834,8 @@ namespace mxg {
 mx_status matmul_pair(const Product &f32, const Product &bf16, int elem, hipStream_t stream)
 {
     Args A0, A1;
-    mx_status ok = matmul_args(A0, f32.a, f32.as, f32.b, f32.bs, f32.M, f32.N, f32.K, 32, elem,
-                               f32.gain, MX_OUT_F32, f32.out, stream);
-    if (ok == MX_OK)
-        ok = matmul_args(A1, bf16.a, bf16.as, bf16.b, bf16.bs, bf16.M, bf16.N, bf16.K, 32, elem,
-                         bf16.gain, MX_OUT_BF16, bf16.out, stream);
-    if (ok != MX_OK)
-        return ok;
+    product_args(A0, f32, elem, stream);
+    product_args(A1, bf16, elem, stream);
     const hipError_t e = elem == MX_ELEM_E4M3 ? multiply_pair<MX_ELEM_E4M3>(A0, A1, stream)
                                               : multiply_pair<MX_ELEM_E2M1>(A0, A1, stream);
     return e == hipSuccess ? MX_OK
@@ -905,11 +908,12 @@ mx_status mxt_matmul(const uint8_t *a_codes, const uint8_t *a_scales, const uint
                      hipStream_t stream)
 {
     mxk::clear_error();
-    mxg::Args A;
-    const mx_status ok = matmul_args(A, a_codes, a_scales, b_codes, b_scales, M, N, K, 32, elem,
-                                     b_gain, out_dtype, out, stream);
+    const mxg::Product P0{a_codes, a_scales, b_codes, b_scales, M, N, K, b_gain, out};
+    const mx_status ok = mxg::check_product(P0, 32, elem, out_dtype);
     if (ok != MX_OK || M == 0 || N == 0)
         return ok;
+    mxg::Args A;
+    product_args(A, P0, elem, stream);
     const int64_t cells = ((M + mxg::BM - 1) / mxg::BM) * ((N + mxg::BN - 1) / mxg::BN);
     if (!known_shape(shape) || whole < 0 || whole >= cells || units < 0 || units > A.grid_max)
         return mxk::fail(MX_EINVAL, "no such tile shape, first launch or number of units");
@@ -926,14 +930,17 @@ mx_status mxt_matmul_pair(const MxtProduct *f32, const MxtProduct *bf16, int ele
                           int units, hipStream_t stream)
 {
     mxk::clear_error();
-    mxg::Args A0, A1;
-    mx_status ok = matmul_args(A0, f32->a, f32->as, f32->b, f32->bs, f32->M, f32->N, f32->K, 32,
-                               elem, f32->gain, MX_OUT_F32, f32->out, stream);
+    const mxg::Product p0{f32->a, f32->as, f32->b, f32->bs, f32->M, f32->N, f32->K, f32->gain, f32->out};
+    const mxg::Product p1{bf16->a, bf16->as, bf16->b, bf16->bs, bf16->M, bf16->N, bf16->K, bf16->gain,
+                          bf16->out};
+    mx_status ok = mxg::check_product(p0, 32, elem, MX_OUT_F32);
     if (ok == MX_OK)
-        ok = matmul_args(A1, bf16->a, bf16->as, bf16->b, bf16->bs, bf16->M, bf16->N, bf16->K, 32,
-                         elem, bf16->gain, MX_OUT_BF16, bf16->out, stream);
+        ok = mxg::check_product(p1, 32, elem, MX_OUT_BF16);
     if (ok != MX_OK)
         return ok;
+    mxg::Args A0, A1;
+    product_args(A0, p0, elem, stream);
+    product_args(A1, p1, elem, stream);
     if (f32->M == 0 || f32->N == 0 || bf16->M == 0 || bf16->N == 0 || units < 0 ||
         units > A0.grid_max)
         return mxk::fail(MX_EINVAL, "empty product, or no such number of units");

@@ -32,6 +32,7 @@
 
 #include "mxnorm.h"
 #include "norm_cast.h"
+#include "products.h"
 #include "status.h"
 #include "testing.h"
 
@@ -371,6 +372,39 @@ mx_status check_p_coef(int p, float &coef, int block)
 
 } // namespace
 
+namespace mxk {
+
+mx_status check_mxnorm(const void *x, int64_t T, int64_t d, int block, int elem, int p, float &coef,
+                       float eps, int scale_mode, const uint8_t *codes, const uint8_t *scales,
+                       const float *rho)
+{
+    if (mx_format(block, elem) < 0)
+        return fail(MX_EINVAL, "block must be 16, 32 or 64 and elem E4M3 or E2M1");
+    mx_status st = check_common(x, nullptr, T, d, block, eps, codes, scales, rho);
+    if (st != MX_OK)
+        return st;
+    if ((st = check_p_coef(p, coef, block)) != MX_OK)
+        return st;
+    if (scale_mode != MX_SCALE_RCEIL && scale_mode != MX_SCALE_FLOOR)
+        return fail(MX_EINVAL, "unknown scale_mode %d", scale_mode);
+    return MX_OK;
+}
+
+mx_status check_cast(const void *x, const void *gamma, int64_t T, int64_t d, int block, int elem,
+                     int scale_mode, const uint8_t *codes, const uint8_t *scales)
+{
+    if (mx_format(block, elem) < 0)
+        return fail(MX_EINVAL, "block must be 16, 32 or 64 and elem E4M3 or E2M1");
+    const mx_status st = check_common(x, gamma, T, d, block, 0.0f, codes, scales, nullptr);
+    if (st != MX_OK)
+        return st;
+    if (scale_mode != MX_SCALE_RCEIL && scale_mode != MX_SCALE_FLOOR)
+        return fail(MX_EINVAL, "unknown scale_mode %d", scale_mode);
+    return MX_OK;
+}
+
+} // namespace mxk
+
 extern "C" {
 
 mx_status mxnorm_mxfp8_fwd(const void *x, int64_t T, int64_t d, int p, float coef, float eps,
@@ -442,16 +476,10 @@ mx_status mxnorm_mx_fwd(const void *x, int64_t T, int64_t d, int block, int elem
                         float *rho, hipStream_t stream)
 {
     clear_error();
-    const int fmt = mx_format(block, elem);
-    if (fmt < 0)
-        return fail(MX_EINVAL, "block must be 16, 32 or 64 and elem E4M3 or E2M1");
-    mx_status st = check_common(x, nullptr, T, d, block, eps, codes, scales, rho);
+    const mx_status st = check_mxnorm(x, T, d, block, elem, p, coef, eps, scale_mode, codes, scales, rho);
     if (st != MX_OK)
         return st;
-    if ((st = check_p_coef(p, coef, block)) != MX_OK)
-        return st;
-    if (scale_mode != MX_SCALE_RCEIL && scale_mode != MX_SCALE_FLOOR)
-        return fail(MX_EINVAL, "unknown scale_mode %d", scale_mode);
+    const int fmt = mx_format(block, elem);
     return run(make_args(x, nullptr, T, d, block, p, coef, eps, scale_mode, 1.0f, codes, scales,
                          rho),
                fmt, K_MXN, stream);
@@ -517,14 +545,10 @@ mx_status mx_cast_fwd(const void *x, const void *gamma, int64_t T, int64_t d, in
                       int elem, int scale_mode, uint8_t *codes, uint8_t *scales, hipStream_t stream)
 {
     clear_error();
-    const int fmt = mx_format(block, elem);
-    if (fmt < 0)
-        return fail(MX_EINVAL, "block must be 16, 32 or 64 and elem E4M3 or E2M1");
-    mx_status st = check_common(x, gamma, T, d, block, 0.0f, codes, scales, nullptr);
+    const mx_status st = check_cast(x, gamma, T, d, block, elem, scale_mode, codes, scales);
     if (st != MX_OK)
         return st;
-    if (scale_mode != MX_SCALE_RCEIL && scale_mode != MX_SCALE_FLOOR)
-        return fail(MX_EINVAL, "unknown scale_mode %d", scale_mode);
+    const int fmt = mx_format(block, elem);
     return run(make_args(x, gamma, T, d, block, 2, 1.0f, 0.0f, scale_mode, 1.0f, codes, scales,
                          nullptr),
                fmt, K_CAST, stream);

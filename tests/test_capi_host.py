@@ -394,3 +394,47 @@ def test_pair_estimates_count_the_plans_that_run(T, N, d):
 ])
 def test_product_plan_at_few_k_steps(M, N, K, elem, shape):
     assert launch_rules.shape_of(M, N, K, elem) == shape
+
+
+W256 = ctypes.c_void_p(0x100000)                      # a 256-byte aligned workspace
+
+
+@pytest.mark.parametrize("kw,status", [
+    (dict(block=16), 2), (dict(block=64), 2), (dict(d=1000), 1), (dict(d=1056), 2), (dict(N=24), 2),
+    (dict(w=None), 1), (dict(ws=OUT + 2), 1), (dict(out=None), 1), (dict(out=A8), 1),
+    (dict(out_dtype=2), 1), (dict(N=-16), 1), (dict(elem=2), 1), (dict(T=0, d=1056), 2),
+    (dict(T=0, x=None, out=None), 0), (dict(T=0, x=None, w=None, out=None), 0),
+])
+def test_linear_forward_checks_both_parts_before_a_launch(kw, status):
+    # what only the product refuses is refused before the norm is launched (a
+    # launch without a GPU would give MX_EHIP)
+    a = dict(x=A16, T=8, d=1024, w=A16, ws=OUT, N=64, block=32, elem=0, out_dtype=0, out=A16)
+    a.update(kw)
+    got = mxnorm.load().mxnorm_linear_fwd(a["x"], a["T"], a["d"], a["w"], a["ws"], a["N"], a["block"],
+                                          a["elem"], 2, 0.0, 1e-6, 0, a["out_dtype"], a["out"], A16,
+                                          W256, 1 << 40, None)
+    assert got == status
+    assert (mxnorm.mx_last_error() != "") == (status != 0)
+
+
+@pytest.mark.parametrize("kw,status", [
+    (dict(block=16), 2), (dict(block=64), 2), (dict(elem=2), 1), (dict(out_dtype=2), 1),
+    (dict(T=96), 2), (dict(T=48), 1), (dict(T=128, elem=1), 2), (dict(N=96), 2), (dict(N=128, elem=1), 2),
+    (dict(d=24), 2), (dict(d=12), 1), (dict(d=65536), 2), (dict(N=65536), 2), (dict(T=1 << 23), 2),
+    (dict(grad_h=None), 1), (dict(x=None), 1), (dict(rho=None), 1), (dict(w=None), 1),
+    (dict(grad_x=None), 1), (dict(grad_w=None), 1), (dict(grad_h=A8), 1), (dict(x=A8), 1),
+    (dict(w=A8), 1), (dict(rho=OUT + 2), 1), (dict(gamma=A8), 1), (dict(grad_x=A8), 1),
+    (dict(grad_w=A8), 1), (dict(grad_gamma=OUT + 2), 1), (dict(T=0), 1), (dict(N=0), 1), (dict(d=0), 1),
+])
+def test_linear_backward_checks_every_part_before_a_launch(kw, status):
+    # up to four kernels used to run before a part refused its arguments, the
+    # row cast with blocks of 16 writing past its scales' place in the workspace
+    a = dict(grad_h=A16, x=A16, rho=A16, gamma=A16, w=A16, T=256, N=512, d=256, block=32, elem=0,
+             out_dtype=0, grad_x=A16, grad_gamma=A16, grad_w=A16)
+    a.update(kw)
+    got = mxnorm.load().mxnorm_linear_bwd(a["grad_h"], a["x"], a["rho"], a["gamma"], a["w"], a["T"],
+                                          a["N"], a["d"], a["block"], a["elem"], a["out_dtype"],
+                                          a["grad_x"], a["grad_gamma"], a["grad_w"], W256, 1 << 60,
+                                          None)
+    assert got == status
+    assert mxnorm.mx_last_error() != ""

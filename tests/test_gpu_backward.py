@@ -290,6 +290,7 @@ def test_mxnorm_linear_backward(elem):
     (4352, 6400, 4128),     # 425 and 289 tiles, the last column of cells 32 wide
     (8192, 2560, 2080),     # 90 and 288 tiles
     (1280, 12544, 544),     # grad_H's cast in XCD ranges, with a partial group
+    (256, 256, 16), (512, 256, 48), (256, 768, 272),   # d an odd multiple of 16
 ])
 def test_linear_backward_equals_its_parts(elem, T, N, d):
     # the one-call backward against the library's own entry points called one
@@ -301,7 +302,7 @@ def test_linear_backward_equals_its_parts(elem, T, N, d):
     rnd = lambda *s: torch.randn(*s, generator=g, device=DEV).to(torch.bfloat16)
     x, gh, w = rnd(T, d), 0.01 * rnd(T, N), 0.02 * rnd(N, d)
     gam = 1 + 0.1 * rnd(d)
-    _, _, rho = mxnorm.mxnorm_mx_fwd(x, elem=elem)
+    _, _, rho = mxnorm.mxnorm_mx_fwd(x, block=16 if d % 32 else 32, elem=elem)
     gx, gg, gw = mxnorm.mxnorm_linear_bwd(gh, x, rho, gam, w, elem=elem, grad_x_dtype=torch.float32)
     a, as_ = mxnorm.mx_cast_fwd(gh, None, elem=elem)
     b, bs = mxnorm.mx_cast_t_fwd(w, None, elem=elem)
