@@ -8,6 +8,7 @@ import numpy as np
 import pytest
 import torch
 
+import launch_rules
 import oracle
 from paper_2603_13180_amd import mxnorm, synth
 
@@ -230,10 +231,54 @@ def test_matmul_column_gain(elem):
 
 # ------------------------------------------------------- whole backward --
 
+def linear_bwd_pieces(gh, x, rho, gamma, w, elem, grad_x_dtype):
+    """mxnorm_linear_bwd through the C entry point with a workspace of its own:
+    (grad_x, grad_gamma, grad_w, pieces), pieces the intermediate operands
+    where the library lays them out, each at a 256-byte boundary."""
+    T, N = gh.shape
+    d = x.shape[1]
+    lib, e = mxnorm.load(), mxnorm.ELEMS[elem]
+    half = 2 if elem == "e2m1" else 1
+    gx = torch.empty(T, d, dtype=grad_x_dtype, device=DEV)
+    gg, gw = torch.empty(d, device=DEV), torch.empty(N, d, device=DEV)
+    ws = torch.full((lib.mxnorm_linear_bwd_workspace_bytes(T, N, d, e),), 0xA5, dtype=torch.uint8,
+                    device=DEV)
+    mxnorm._check(lib.mxnorm_linear_bwd(
+        gh.data_ptr(), x.data_ptr(), rho.data_ptr(), mxnorm._ptr(gamma), w.data_ptr(), T, N, d, 32, e,
+        mxnorm.OUT_DTYPES[grad_x_dtype], gx.data_ptr(), gg.data_ptr(), gw.data_ptr(), ws.data_ptr(),
+        ws.numel(), mxnorm._stream(ws.device)))
+    torch.cuda.synchronize()
+    pieces, at = {}, 0
+    for name, rows, cols in (("gh", T, N // half), ("gh_s", T, N // 32), ("wt", d, N // half),
+                             ("wt_s", d, N // 32), ("ght", N, T // half), ("ght_s", N, T // 32),
+                             ("xt", d, T // half), ("xt_s", d, T // 32), ("gz", T, 2 * d)):
+        pieces[name] = ws[at:at + rows * cols].view(rows, cols)
+        at += -(-rows * cols // 256) * 256
+    pieces["gz"] = pieces["gz"].view(torch.bfloat16)
+    return gx, gg, gw, pieces
+
+
+def same_bytes(t, want, ctx):
+    got = t.cpu().numpy()
+    bad = np.argwhere(got != want)
+    assert bad.size == 0, "%s: %d bytes differ, first %s got %#x want %#x" % (
+        ctx, len(bad), bad[0], got[tuple(bad[0])], want[tuple(bad[0])])
+
+
+# (T, N, d) and how the two products are computed there: in one launch of 64 x
+# 128 tiles with 2 K steps each, the smallest; with 8 and 18, 6 and 10, 6 and 4
+# steps (E4M3: a ring of 3 slots comes round; either product first; d and N
+# beside whole tiles); or, in 8 bits, one after the other
+BACKWARDS = [(256, 256, 512, "small", "small"), (1024, 2304, 768, "small", "small"),
+             (768, 1280, 416, "small", "small"), (768, 512, 416, "small", "small"),
+             (512, 768, 288, "apart", "small")]
+
+
 @pytest.mark.parametrize("elem", ["e4m3", "e2m1"])
-def test_mxnorm_linear_backward(elem):
-    from test_gpu_gemm import abs_codes, assert_close
-    T, d, N = 256, 512, 256
+@pytest.mark.parametrize("T,N,d,way8,way4", BACKWARDS)
+def test_mxnorm_linear_backward(elem, T, N, d, way8, way4):
+    from test_gpu_gemm import abs_codes, assert_close, oracle_product
+    assert launch_rules.pair_plan(T, N, d, elem)[0] == (way8 if elem == "e4m3" else way4)
     rng = np.random.default_rng(17)
     xb = synth.gaussian(T, d, seed=21, scale=1.3)
     whb = synth.f32_to_bf16_bits((0.05 * rng.standard_normal((N, d))).astype(np.float32))
@@ -241,37 +286,41 @@ def test_mxnorm_linear_backward(elem):
     gb = synth.f32_to_bf16_bits(rng.uniform(0.5, 1.5, d).astype(np.float32))
     x, w, gh, g = dev_bf16(xb), dev_bf16(whb), dev_bf16(ghb), dev_bf16(gb)
     _, _, rho = mxnorm.mxnorm_mx_fwd(x, block=32, elem=elem)
-    gx, gg, gw = mxnorm.mxnorm_linear_bwd(gh, x, rho, g, w, elem=elem,
-                                          grad_x_dtype=torch.float32)
-    torch.cuda.synchronize()
+    gx, gg, gw, P = linear_bwd_pieces(gh, x, rho, g, w, elem, torch.float32)
     rho_np = rho.cpu().numpy()
 
-    # stage 1: grad_Z = MXCast(grad_H) MXCast_N(W)
+    # the Python call is the same call: deterministic, so the same bits
+    for a, b in zip((gx, gg, gw), mxnorm.mxnorm_linear_bwd(gh, x, rho, g, w, elem=elem,
+                                                          grad_x_dtype=torch.float32)):
+        assert torch.equal(a, b)
+
+    # the casts, bit for bit
     hc, hs = oracle.mxcast_gain(ghb, None, B=32, elem=elem)
     wc, ws = oracle.mxcast_t(whb, None, B=32, elem=elem)
-    gz_o = oracle.mx_matmul(hc, hs, wc, ws, N, elem=elem)
-    gz_mag = oracle.mx_matmul(abs_codes(hc, elem), hs, abs_codes(wc, elem), ws, N, elem=elem)
-    gh_c, gh_s = mxnorm.mx_cast_fwd(gh, None, elem=elem)
-    wt_c, wt_s = mxnorm.mx_cast_t_fwd(w, None, elem=elem)
-    gz = mxnorm.mx_matmul_fwd(gh_c, gh_s, wt_c, wt_s, N, elem=elem, out_dtype=torch.bfloat16)
-    torch.cuda.synchronize()
-    assert np.array_equal(gh_c.cpu().numpy(), hc) and np.array_equal(wt_c.cpu().numpy(), wc)
-    assert_close(gz.float().cpu().numpy().astype(np.float64), gz_o, gz_mag, True, "grad_Z")
+    tc, ts = oracle.mxcast_t(ghb, None, B=32, elem=elem)
+    xc, xs = oracle.mxcast_t(xb, rho_np, B=32, elem=elem)
+    for name, want in (("gh", hc), ("gh_s", hs), ("wt", wc), ("wt_s", ws), ("ght", tc),
+                       ("ght_s", ts), ("xt", xc), ("xt_s", xs)):
+        same_bytes(P[name], want, "%s %s" % (elem, name))
+
+    # stage 1: grad_Z = MXCast(grad_H) MXCast_N(W)
+    gz_o, gz_mag = oracle_product(hc, hs, wc, ws, N, elem)
+    assert_close(P["gz"].float().cpu().numpy().astype(np.float64), gz_o, gz_mag, True, "grad_Z")
 
     # stage 2: the STE on that grad_Z
-    wx, wg = oracle.ste_bwd(xb, bits_of(gz), gb, rho_np)
-    terms, gsum = ste_bounds(xb, bits_of(gz), gb, rho_np)
+    gzb = bits_of(P["gz"])
+    wx, wg = oracle.ste_bwd(xb, gzb, gb, rho_np)
+    terms, gsum = ste_bounds(xb, gzb, gb, rho_np)
     assert (np.abs(gx.cpu().numpy() - wx) <= 2.0 ** -21 * terms + 2.0 ** -22 * np.abs(wx)
             + 1e-37).all()
     assert (np.abs(gg.cpu().numpy() - wg) <= 2.0 ** -16 * gsum + 1e-37).all()
 
     # stage 3: grad_W = (MXCast(grad_H^T) MXCast(rho~ X)^T) gamma
-    tc, ts = oracle.mxcast_t(ghb, None, B=32, elem=elem)
-    xc, xs = oracle.mxcast_t(xb, rho_np, B=32, elem=elem)
-    gw_o = oracle.mx_matmul(tc, ts, xc, xs, T, elem=elem) * f64(gb)[None, :]
-    gw_mag = oracle.mx_matmul(abs_codes(tc, elem), ts, abs_codes(xc, elem), xs, T,
-                              elem=elem) * np.abs(f64(gb))[None, :]
+    gw_o, gw_mag = oracle_product(tc, ts, xc, xs, T, elem)
+    gw_o, gw_mag = gw_o * f64(gb)[None, :], gw_mag * np.abs(f64(gb))[None, :]
     assert_close(gw.cpu().numpy().astype(np.float64), gw_o, gw_mag, False, "grad_W")
+    if (T, N, d) != (256, 256, 512):
+        return
 
     # and the whole thing approximates the float64 RMSNorm-linear gradient:
     # the oracle's own chain is 5.6% (E4M3) and 16.8% (E2M1) away here, from
@@ -285,11 +334,12 @@ def test_mxnorm_linear_backward(elem):
 
 @pytest.mark.parametrize("elem", ["e4m3", "e2m1"])
 @pytest.mark.parametrize("T,N,d", [
-    (256, 512, 256),        # small products, one launch each
+    (256, 512, 256),        # one launch each in 8 bits, a shared one of small tiles in 4
+    (1024, 2304, 768),      # a shared launch of small tiles, several K steps
     (4096, 6144, 4096),     # 384 and 256 tiles: both products in one launch
     (4352, 6400, 4128),     # 425 and 289 tiles, the last column of cells 32 wide
     (8192, 2560, 2080),     # 90 and 288 tiles
-    (1280, 12544, 544),     # grad_H's cast in XCD ranges, with a partial group
+    (1280, 12544, 544),     # one launch each; grad_H's cast in XCD ranges, with a partial group
     (256, 256, 16), (512, 256, 48), (256, 768, 272),   # d an odd multiple of 16
 ])
 def test_linear_backward_equals_its_parts(elem, T, N, d):
@@ -320,8 +370,10 @@ def test_linear_backward_equals_its_parts(elem, T, N, d):
 
 @pytest.mark.parametrize("elem", ["e4m3", "e2m1"])
 def test_linear_backward_special_values(elem):
-    # zero rows and columns, subnormals, an infinity and a NaN in grad_H: the
-    # one-call backward has the parts' NaNs, and their values elsewhere
+    # zero rows and columns, subnormals, an infinity and a NaN in grad_H, zeros
+    # and subnormals in W and X: the one-call backward's codes and scales are
+    # the parts' bytes (the oracle's for grad_H and W), it has the parts' NaNs,
+    # and their values elsewhere
     T, N, d = 512, 768, 288
     g = torch.Generator(device=DEV)
     g.manual_seed(9)
@@ -330,10 +382,22 @@ def test_linear_backward_special_values(elem):
     gh[7], gh[:, 33] = 0, 0
     gh[64:96, 128:160] *= 2.0 ** -126
     gh[3, 5], gh[200, 700] = float("nan"), float("-inf")
+    w[:, 9], w[32:64, 40:72] = 0, w[32:64, 40:72] * 2.0 ** -126
+    x[64:128, 100:140] *= 2.0 ** -126
     _, _, rho = mxnorm.mxnorm_mx_fwd(x, elem=elem)
-    gx, gg, gw = mxnorm.mxnorm_linear_bwd(gh, x, rho, gam, w, elem=elem, grad_x_dtype=torch.float32)
+    gx, gg, gw, P = linear_bwd_pieces(gh, x, rho, gam, w, elem, torch.float32)
     a, as_ = mxnorm.mx_cast_fwd(gh, None, elem=elem)
     b, bs = mxnorm.mx_cast_t_fwd(w, None, elem=elem)
+    at, at_s = mxnorm.mx_cast_t_fwd(gh, None, elem=elem)
+    xt, xt_s = mxnorm.mx_cast_t_fwd(x, rho, elem=elem)
+    for name, want in (("gh", a), ("gh_s", as_), ("wt", b), ("wt_s", bs), ("ght", at),
+                       ("ght_s", at_s), ("xt", xt), ("xt_s", xt_s)):
+        same_bytes(P[name], want.cpu().numpy(), "%s %s" % (elem, name))
+    for (c, sc), (oc, os_) in (((a, as_), oracle.mxcast_gain(bits_of(gh), None, B=32, elem=elem)),
+                               ((at, at_s), oracle.mxcast_t(bits_of(gh), None, B=32, elem=elem)),
+                               ((b, bs), oracle.mxcast_t(bits_of(w), None, B=32, elem=elem))):
+        same_bytes(c, oc, elem)
+        same_bytes(sc, os_, elem)
     gz = mxnorm.mx_matmul_fwd(a, as_, b, bs, N, elem=elem, out_dtype=torch.bfloat16)
     wx, _ = mxnorm.mxnorm_ste_bwd(x, gz, gam, rho, out_dtype=torch.float32)
     a, as_ = mxnorm.mx_cast_t_fwd(gh, None, elem=elem)
@@ -347,6 +411,39 @@ def test_linear_backward_special_values(elem):
         assert torch.equal(torch.isnan(got), nan), name
         err = float((got - want)[~nan].norm() / want[~nan].norm())
         assert err <= (1e-6 if name == "grad_w" else 1e-4), (name, err)
+
+
+@pytest.mark.parametrize("elem", ["e4m3", "e2m1"])
+def test_linear_backward_large_tiles_sampled(elem):
+    # 425 and 289 tiles of 256 x 256 in one launch, shared out by load, the last
+    # column of them 32 wide: sampled rows of grad_Z and grad_W, every column,
+    # against the oracle's products of the call's own operands (which are the
+    # parts' bytes)
+    from test_gpu_gemm import assert_close, oracle_product, tile_sample
+    T, N, d = 4352, 6400, 4128
+    assert launch_rules.pair_plan(T, N, d, elem)[0] == "large"
+    g = torch.Generator(device=DEV)
+    g.manual_seed(5)
+    rnd = lambda *s: torch.randn(*s, generator=g, device=DEV).to(torch.bfloat16)
+    x, gh, w, gam = rnd(T, d), 0.01 * rnd(T, N), 0.02 * rnd(N, d), 1 + 0.1 * rnd(d)
+    _, _, rho = mxnorm.mxnorm_mx_fwd(x, elem=elem)
+    _, _, gw, P = linear_bwd_pieces(gh, x, rho, gam, w, elem, torch.bfloat16)
+    for names, cast in ((("gh", "gh_s"), mxnorm.mx_cast_fwd(gh, None, elem=elem)),
+                        (("ght", "ght_s"), mxnorm.mx_cast_t_fwd(gh, None, elem=elem)),
+                        (("wt", "wt_s"), mxnorm.mx_cast_t_fwd(w, None, elem=elem)),
+                        (("xt", "xt_s"), mxnorm.mx_cast_t_fwd(x, rho, elem=elem))):
+        for n, t in zip(names, cast):
+            assert torch.equal(P[n], t), n
+    H = {k: v.cpu().numpy() for k, v in P.items() if k != "gz"}
+    rows = tile_sample(T, lead=2, extra=4)
+    want, mag = oracle_product(H["gh"][rows], H["gh_s"][rows], H["wt"], H["wt_s"], N, elem)
+    got = P["gz"][torch.from_numpy(rows).to(DEV)].float().cpu().numpy().astype(np.float64)
+    assert_close(got, want, mag, True, "grad_Z %s" % elem)
+    rows = tile_sample(N, lead=2, extra=4)
+    want, mag = oracle_product(H["ght"][rows], H["ght_s"][rows], H["xt"], H["xt_s"], T, elem)
+    f = gam.double().cpu().numpy()
+    got = gw[torch.from_numpy(rows).to(DEV)].cpu().numpy().astype(np.float64)
+    assert_close(got, want * f, mag * np.abs(f), False, "grad_W %s" % elem)
 
 
 def test_transpose_stream_reference_moves_the_bytes():
