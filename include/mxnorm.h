@@ -200,6 +200,12 @@ typedef enum {
  * one instruction, products far below the largest one can be dropped; the
  * total error stays within 2^-9 of sum_k |A[m][k] B[n][k]|).  A NaN scale or
  * code gives NaN; results beyond the float range are infinite.
+ * The order of the additions depends on M, N, K, elem and the device's number
+ * of compute units: most outputs are summed over K in order, but where few
+ * tiles would leave compute units idle (decoding steps, small matrices) eight
+ * partial sums over interleaved parts of K are added.  The same call on the
+ * same device gives the same bits; a row of H may differ in its last float
+ * bits between calls with another M, so a token's H may depend on its batch.
  * block: 32 (other sizes: MX_EUNSUPPORTED).  elem: mx_elem.  Requirements:
  * K a multiple of 128 (E4M3) or 256 (E2M1) and at most MX_MATMUL_MAX_K, N a
  * multiple of 16 and at most MX_MATMUL_MAX_N (else MX_EUNSUPPORTED); codes
@@ -281,8 +287,9 @@ mx_status mxnorm_ste_bwd_noalloc(const void *x, const void *grad_z, const void *
  * The MXNormLinear forward (Sec. 3.7 eq. (mx-matmul); the implementation
  * appendix's mx_norm_linear_forward) as one call: mxnorm_mx_fwd of x [T, d],
  * then mx_matmul_fwd with a weight cast once by mx_cast_fwd (codes and scales
- * [N, .]).  Same arguments, arithmetic, outputs and errors as the two calls;
- * out [T, N] in out_dtype, rho float [T] or NULL.  The activation codes and
+ * [N, .]).  Same arguments, outputs (bit for bit) and errors as the two calls,
+ * the errors of both before the first launch; out [T, N] in out_dtype, rho
+ * float [T] or NULL.  The activation codes and
  * scales live in `workspace`: caller-owned device memory of
  * mxnorm_linear_fwd_workspace_bytes() bytes, 256-byte aligned, overwritten.
  */
@@ -301,10 +308,14 @@ mx_status mxnorm_linear_fwd(const void *x, int64_t T, int64_t d, const uint8_t *
  *   grad_W = (MXCast(grad_H^T) MXCast(rho~ X)^T) . gamma   (float32)
  * grad_h: bf16 [T, N]; x: bf16 [T, d]; rho: float [T]; gamma: bf16 [d] or
  * NULL; w: bf16 [N, d]; grad_x [T, d] in out_dtype, grad_gamma float [d],
- * grad_w float [N, d].  RCEIL scales.  Values and errors are those of
- * mx_cast_fwd, mx_cast_t_fwd, mx_matmul_fwd and mxnorm_ste_bwd called one by
- * one.  `workspace`: caller-owned device memory of
- * mxnorm_linear_bwd_workspace_bytes() bytes, 256-byte aligned, overwritten.
+ * grad_w float [N, d].  RCEIL scales.  The codes and scales are the bytes of
+ * mx_cast_fwd and mx_cast_t_fwd, and the refusals those of these two,
+ * mx_matmul_fwd and mxnorm_ste_bwd, all before the first launch.  The products
+ * are within mx_matmul_fwd's bound but may be summed in another order than its
+ * calls (they can share a launch with other tiles): grad_Z, rounded to bf16,
+ * then differs by one unit in rare elements.  `workspace`: caller-owned device
+ * memory of mxnorm_linear_bwd_workspace_bytes() bytes, 256-byte aligned,
+ * overwritten.
  */
 size_t mxnorm_linear_bwd_workspace_bytes(int64_t T, int64_t N, int64_t d, int elem);
 mx_status mxnorm_linear_bwd(const void *grad_h, const void *x, const float *rho,

@@ -35,7 +35,8 @@ struct Product {
 mx_status check_product(const Product &P, int block, int elem, int out_dtype);
 
 // A product with float output and one with bf16 output that do not depend on
-// each other, on one stream.  Values as two mx_matmul_fwd calls.
+// each other, on one stream: within mx_matmul_fwd's bound, in one launch or
+// two, so the sums may be taken in another order than by two mx_matmul_fwd calls.
 mx_status matmul_pair(const Product &f32, const Product &bf16, int elem, hipStream_t stream);
 
 } // namespace mxg

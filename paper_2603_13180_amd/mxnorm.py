@@ -292,7 +292,8 @@ def mx_matmul_fwd(a_codes, a_scales, b_codes, b_scales, K, block=32, elem="e4m3"
     """H = dec(A) dec(B)^T on the block-scaled matrix cores (Sec. 3.7 eq.
     (mx-matmul)).  A: MX codes/scales [M, .] along K; B: [N, .].  b_gain
     (bf16 [N]) multiplies column n of H after the product.  Returns H [M, N]
-    in out_dtype (float32 or bfloat16)."""
+    in out_dtype (float32 or bfloat16).  The order of the float additions, and
+    with it a row's last bits, may depend on M, N and K."""
     if elem not in ELEMS or out_dtype not in OUT_DTYPES:
         raise ValueError("elem must be 'e4m3' or 'e2m1', out_dtype float32 or bfloat16")
     M = _mx_operand(a_codes, a_scales, K, block, elem, "A")

@@ -186,6 +186,20 @@ def test_mxnorm_linear_forward(block_elem, T, d, N):
                  "mxnorm_linear %s T=%d d=%d N=%d" % (elem, T, d, N))
 
 
+@pytest.mark.parametrize("elem", ELEMS)
+@pytest.mark.parametrize("out_dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("T,d,N", [(1, 256, 64), (61, 1024, 272), (700, 2048, 1040)])
+def test_linear_forward_is_its_two_parts(elem, out_dtype, T, d, N):
+    g = torch.Generator(device=DEV).manual_seed(T)
+    x = torch.randn(T, d, generator=g, device=DEV).to(torch.bfloat16)
+    w = (0.02 * torch.randn(N, d, generator=g, device=DEV)).to(torch.bfloat16)
+    wc, ws = mxnorm.mx_cast_fwd(w, None, elem=elem)
+    h, rho = mxnorm.mxnorm_linear_fwd(x, wc, ws, elem=elem, out_dtype=out_dtype)
+    c, s, r = mxnorm.mxnorm_mx_fwd(x, elem=elem)
+    assert torch.equal(rho, r)
+    assert torch.equal(h, mxnorm.mx_matmul_fwd(c, s, wc, ws, d, elem=elem, out_dtype=out_dtype))
+
+
 # ------------------------------------------- the benchmarked shapes --
 #
 # At these sizes the kernel maps workgroups to 256 x 256 output tiles through an

@@ -134,6 +134,27 @@ def test_every_output(elem, shape, whole, units):
 
 
 @pytest.mark.parametrize("elem", ELEMS)
+def test_only_k_split_changes_the_order_of_additions(elem):
+    # rings, 256 x 256 tiles, tails and pairs add the K steps in order: the same
+    # bits; K-split tiles add eight partial sums, the same for all of them
+    M, N, K = 531, 560, 2560
+    t, _, _, _ = random_case(elem, M, N, K)
+    bits = {}
+    for shape, whole, units in WAYS:
+        if not whole:
+            bits[shape, units] = matmul_as(*t, K, elem, shape, 0, units)
+    want = bits["t256x256", 0]
+    split = bits["k64x64", 0]
+    assert not torch.equal(split, want)
+    for (shape, units), h in bits.items():
+        assert torch.equal(h, split if shape.startswith("k") else want), (shape, units)
+    for mode in ("large", "small"):
+        outs = [torch.empty(M, N, device=DEV), torch.empty(M, N, dtype=torch.bfloat16, device=DEV)]
+        matmul_pair_as(*[(*t, K, None, o) for o in outs], elem, mode)
+        assert torch.equal(outs[0], want) and torch.equal(outs[1], want.to(torch.bfloat16))
+
+
+@pytest.mark.parametrize("elem", ELEMS)
 @pytest.mark.parametrize("shape", SHAPES)
 @pytest.mark.parametrize("M,N,K", [(1, 16, 256), (257, 272, 256), (129, 144, 2816)])
 def test_smallest_and_uneven(elem, shape, M, N, K):
