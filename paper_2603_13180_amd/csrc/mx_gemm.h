@@ -217,6 +217,31 @@ __device__ __forceinline__ void read_frags(Frag (&f)[N], const LDS_AS uint8_t *s
     ((f[J] = read_frag<ELEM, J>(st, b)), ...);
 }
 
+// acc += B-fragment x A-fragment over one K step (B is the instruction's first
+// operand: each lane's four results are then four consecutive columns of one
+// row of H).  E4M3: one instruction.  E2M1: the fragments' low halves, then
+// their high halves.
+__device__ __forceinline__ void mma_e4m3(v4f &acc, const Frag &b, const Frag &a)
+{
+    acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(b.v, a.v, acc, 0, 0, 0, b.s0, 0, a.s0);
+}
+
+__device__ __forceinline__ void mma_e2m1_lo(v4f &acc, const Frag &b, const Frag &a)
+{
+    const v8i z = {0, 0, 0, 0, 0, 0, 0, 0};
+    const v8i b0 = __builtin_shufflevector(b.v, z, 0, 1, 2, 3, 8, 8, 8, 8);
+    const v8i a0 = __builtin_shufflevector(a.v, z, 0, 1, 2, 3, 8, 8, 8, 8);
+    acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(b0, a0, acc, 4, 4, 0, b.s0, 0, a.s0);
+}
+
+__device__ __forceinline__ void mma_e2m1_hi(v4f &acc, const Frag &b, const Frag &a)
+{
+    const v8i z = {0, 0, 0, 0, 0, 0, 0, 0};
+    const v8i b1 = __builtin_shufflevector(b.v, z, 4, 5, 6, 7, 8, 8, 8, 8);
+    const v8i a1 = __builtin_shufflevector(a.v, z, 4, 5, 6, 7, 8, 8, 8, 8);
+    acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(b1, a1, acc, 4, 4, 0, b.s1, 0, a.s1);
+}
+
 // acc[i] += B-fragment i x A-fragment, one K step.  E2M1: the low halves of
 // all tiles before the high ones, so that an accumulator's two instructions
 // are not back to back.
@@ -226,24 +251,14 @@ __device__ __forceinline__ void mma_column(v4f (&acc)[FN], const Frag (&b)[FN], 
     if constexpr (ELEM == MX_ELEM_E4M3) {
 #pragma unroll
         for (int i = 0; i < FN; ++i)
-            acc[i] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(b[i].v, a.v, acc[i], 0, 0, 0,
-                                                                      b[i].s0, 0, a.s0);
+            mma_e4m3(acc[i], b[i], a);
     } else {
-        const v8i z = {0, 0, 0, 0, 0, 0, 0, 0};
-        const v8i a0 = __builtin_shufflevector(a.v, z, 0, 1, 2, 3, 8, 8, 8, 8);
-        const v8i a1 = __builtin_shufflevector(a.v, z, 4, 5, 6, 7, 8, 8, 8, 8);
 #pragma unroll
-        for (int i = 0; i < FN; ++i) {
-            const v8i b0 = __builtin_shufflevector(b[i].v, z, 0, 1, 2, 3, 8, 8, 8, 8);
-            acc[i] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(b0, a0, acc[i], 4, 4, 0,
-                                                                      b[i].s0, 0, a.s0);
-        }
+        for (int i = 0; i < FN; ++i)
+            mma_e2m1_lo(acc[i], b[i], a);
 #pragma unroll
-        for (int i = 0; i < FN; ++i) {
-            const v8i b1 = __builtin_shufflevector(b[i].v, z, 4, 5, 6, 7, 8, 8, 8, 8);
-            acc[i] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(b1, a1, acc[i], 4, 4, 0,
-                                                                      b[i].s1, 0, a.s1);
-        }
+        for (int i = 0; i < FN; ++i)
+            mma_e2m1_hi(acc[i], b[i], a);
     }
 }
 

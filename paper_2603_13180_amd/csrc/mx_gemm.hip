@@ -131,14 +131,6 @@ __device__ __forceinline__ void issue_step(const uint8_t *ta, const uint8_t *tb,
         lds_load4(ts, R.s[u] + ks, xs + u * (64 / DW) * SB);
 }
 
-// acc += B-fragment x A-fragment over one E4M3 K step (B is the
-// instruction's first operand: each lane's four results are then four
-// consecutive columns of one row of H)
-__device__ __forceinline__ void mma_e4m3(v4f &acc, const Frag &b, const Frag &a)
-{
-    acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(b.v, a.v, acc, 0, 0, 0, b.s0, 0, a.s0);
-}
-
 // The products of one K step from the stage at st: the step's four B
 // fragments held in registers, the eight A fragments streamed, each requested
 // two ahead of the products that use it.
@@ -156,19 +148,6 @@ __device__ __forceinline__ void step_products(v4f (&acc)[FN][FM], const LDS_AS u
         // (Two passes over the 32 tiles, every low half and then every high
         // half from half-fragment reads, were 1.5-3% slower at the QKV and
         // gate+up shapes.)
-        const v8i z = {0, 0, 0, 0, 0, 0, 0, 0};
-        auto lo = [&](v4f &acc, const Frag &b, const Frag &a) {
-            const v8i b0 = __builtin_shufflevector(b.v, z, 0, 1, 2, 3, 8, 8, 8, 8);
-            const v8i a0 = __builtin_shufflevector(a.v, z, 0, 1, 2, 3, 8, 8, 8, 8);
-            acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(b0, a0, acc, 4, 4, 0, b.s0, 0,
-                                                                   a.s0);
-        };
-        auto hi = [&](v4f &acc, const Frag &b, const Frag &a) {
-            const v8i b1 = __builtin_shufflevector(b.v, z, 4, 5, 6, 7, 8, 8, 8, 8);
-            const v8i a1 = __builtin_shufflevector(a.v, z, 4, 5, 6, 7, 8, 8, 8, 8);
-            acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(b1, a1, acc, 4, 4, 0, b.s1, 0,
-                                                                   a.s1);
-        };
         Frag fb[FN], fa[FM];
         fb[0] = read_frag<ELEM, 0>(st, bb);
         fb[1] = read_frag<ELEM, 1>(st, bb);
@@ -185,10 +164,10 @@ __device__ __forceinline__ void step_products(v4f (&acc)[FN][FM], const LDS_AS u
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int i = 0; i < FN; ++i)
-                lo(acc[i][j], fb[i], fa[j]);
+                mma_e2m1_lo(acc[i][j], fb[i], fa[j]);
 #pragma unroll
             for (int i = 0; i < FN; ++i)
-                hi(acc[i][j], fb[i], fa[j]);
+                mma_e2m1_hi(acc[i][j], fb[i], fa[j]);
             __builtin_amdgcn_sched_barrier(0);
         };
         column(std::integral_constant<int, 0>{});
