@@ -457,7 +457,7 @@ enum Shape { S_K16x32, S_K32x32, S_K32x64, S_K64x64, S_R64x128, S_R128x128, S_25
 // 256: 9526 x 22336 129 against 106 us, 142102 x 1152 97 against 70.  Counted
 // from the ninth round on for the rings (with fewer rounds 256 x 256 tiles do
 // not reach their pace either: two K steps, 3 to 8 rounds, the rings are 1.05
-// to 1.1 times as fast in the median), from the first if N leaves half of the
+// to 1.4 times as fast in the median of each output type), from the first if N leaves half of the
 // 64 x 128 tile empty (63697 x 48 10.5 against 8.0), and for the K-split tiles
 // beyond two rounds.  Over 1000 sizes of 1 to 4 steps and 1e6 to 2e8 outputs
 // the choice was more than 3% slower than 256 x 256 tiles at 106, by up to 28%,
